@@ -1,0 +1,321 @@
+"""Workloads of the selected-inversion library, as a program that uses it runs them.
+
+A pass is what such a program repeats: the numerical inversion of a matrix whose
+analysis and factors it holds (``run`` and the extraction of the selected
+entries, eagerly or as a graph replay), the same for a batch of matrices, or the
+whole step of a loop that gets new values on a fixed pattern (``factor_device``,
+``run``, extraction).  Matrices are 2D and 3D grid stencils in a geometric
+nested-dissection order, the shapes of this repository's configurations, with
+values drawn from the seed.  The launch choices are the library's own policy
+(no tuning run).
+
+A case is a dict of
+  dims        grid, as a text ("64x64x64"); a batch lists several ("64x64,96x96")
+  stencil     "star" (5/7 points) or "box" (9/27 points)
+  values      "convection", "random", "upwind" (non-symmetric pattern, exact
+              analysis) or "complex"
+  cap, leaf, pad_pct   supernode partition rules
+  precision   "fp64", "mixed_fp32" or "mixed_bf16x3"
+  refactor    whether a pass starts from new values in device memory
+  graph       whether the sweep is replayed from a HIP graph
+"""
+import functools
+import math
+
+import numpy as np
+import torch
+
+from paper_1708_04539_amd.selinv import Batch, SelInv
+
+
+def _case(dims, stencil, values, cap, precision="fp64", leaf=64, refactor=False, graph=True, name=None):
+    c = {"dims": dims, "stencil": stencil, "values": values, "cap": cap, "leaf": leaf,
+         "pad_pct": 50 if values == "upwind" else 5, "precision": precision, "refactor": refactor,
+         "graph": graph}
+    if name:
+        c["name"] = name
+    return c
+
+
+def listed():
+    return [
+        # the smallest matrix anyone inverts: a few launches, all latency
+        _case("32x32", "star", "convection", 32, leaf=32, name="grid2d_32_fp64"),
+        # the ordinary 2D problem, factors in hand: the level chain of short launches
+        _case("256x256", "box", "random", 128, name="grid2d_256_fp64"),
+        # a ragged 2D grid in the mixed form, eager launches
+        _case("193x117", "box", "random", 96, "mixed_fp32", graph=False, name="grid2d_193x117_fp32"),
+        # a loop over new values on a fixed pattern (one pole or one Newton step after another)
+        _case("256x256", "box", "random", 128, refactor=True, name="grid2d_256_refactor"),
+        # many independent small systems in one sweep
+        _case("64x64,201x201,91x91,256x256,120x120,75x75,168x168,139x139,222x222,103x103,83x83,183x183",
+              "star", "convection", 128, name="batch_12_fp64"),
+        # structurally non-symmetric pattern, analysed exactly (R_L != R_U)
+        _case("256x256", "box", "upwind", 128, name="upwind_256_exact"),
+        # complex shifted operator, held in its real form
+        _case("256x256", "box", "complex", 256, leaf=128, name="complex_256_fp64"),
+        # 3D convection-diffusion
+        _case("48x48x48", "star", "convection", 256, name="grid3d_48_fp64"),
+        # a ragged 3D box in mixed FP32, eager launches
+        _case("45x38x31", "box", "random", 384, "mixed_fp32", graph=False, name="grid3d_45x38x31_fp32"),
+        # 3D loop over new values: device LU, inversion and extraction
+        _case("40x40x40", "box", "random", 512, refactor=True, graph=False, name="grid3d_40_refactor"),
+        # the largest: 3D 64^3 27-point, in full precision and in split-BF16
+        _case("64x64x64", "box", "random", 512, name="grid3d_64_fp64"),
+        _case("64x64x64", "box", "random", 512, "mixed_bf16x3", name="grid3d_64_bf16x3"),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["2d", "2d", "2d", "3d", "3d", "3d", "batch", "upwind", "complex"])
+    prec = rng.choice(["fp64", "fp64", "mixed_fp32", "mixed_bf16x3"])
+    refactor = rng.random() < 0.3
+    graph = rng.random() < 0.6
+    stencil = rng.choice(["star", "box"])
+    values = rng.choice(["convection", "random"])
+    if kind == "3d":
+        dims = [_log_int(rng, 8, 56) for _ in range(3)]
+        return _case("x".join(map(str, dims)), stencil, values, rng.randint(96, 512), prec, refactor=refactor,
+                     graph=graph)
+    if kind == "batch":
+        sides = [_log_int(rng, 24, 256) for _ in range(rng.randint(2, 12))]
+        return _case(",".join(f"{s}x{s}" for s in sides), stencil, values, rng.randint(64, 160), prec,
+                     graph=graph)
+    dims = f"{_log_int(rng, 16, 256)}x{_log_int(rng, 16, 256)}"
+    if kind == "upwind":
+        return _case(dims, stencil, "upwind", rng.randint(48, 160), prec, graph=graph)
+    if kind == "complex":
+        return _case(dims, stencil, "complex", 2 * rng.randint(24, 128), prec, leaf=128, refactor=refactor,
+                     graph=graph)
+    return _case(dims, stencil, values, rng.randint(24, 160), prec, leaf=rng.choice([16, 32, 64]),
+                 refactor=refactor, graph=graph)
+
+
+# ---------------------------------------------------------------------------
+# matrices
+# ---------------------------------------------------------------------------
+
+def _grids(case):
+    return [tuple(int(x) for x in g.split("x")) for g in case["dims"].split(",")]
+
+
+@functools.lru_cache(maxsize=24)
+def _order(dims, leaf):
+    """Nested dissection, perm[new] = old: split the longest axis (the first of
+    equals) in the middle, left box, right box, separator; leaves in grid order."""
+    d3 = dims + (1,) * (3 - len(dims))
+    ids = np.arange(d3[0] * d3[1] * d3[2], dtype=np.int32).reshape(d3[::-1])
+    out = []
+
+    def rec(box):
+        if box.size == 0:
+            return
+        if box.size <= leaf:
+            out.append(box.ravel())
+            return
+        ext = box.shape[::-1]
+        ax = 2 - ext.index(max(ext))
+        m = box.shape[ax] // 2
+        rec(box.take(range(m), ax))
+        rec(box.take(range(m + 1, box.shape[ax]), ax))
+        out.append(box.take([m], ax).ravel())
+
+    rec(ids)
+    return np.concatenate(out)
+
+
+@functools.lru_cache(maxsize=24)
+def _pattern(dims, stencil, values):
+    """Entries offset by offset: rows, columns, direction (sign of the offset),
+    and the CSC order, column pointers and row indices (diagonal entries last
+    in the entry list)."""
+    nx, ny, nz = dims + (1,) * (3 - len(dims))
+    n = nx * ny * nz
+    ids = np.arange(n, dtype=np.int32).reshape(nz, ny, nx)
+    rng = np.random.default_rng(97)  # which downstream couplings an upwind pattern keeps
+    rows, cols, sign = [], [], []
+    for dz in (-1, 0, 1) if nz > 1 else (0,):
+        for dy in (-1, 0, 1):
+            for dx in (-1, 0, 1):
+                off = (dx, dy, dz)
+                if off == (0, 0, 0) or (stencil == "star" and sum(map(abs, off)) != 1):
+                    continue
+                i = ids[max(0, -dz):nz - max(0, dz), max(0, -dy):ny - max(0, dy), max(0, -dx):nx - max(0, dx)].ravel()
+                j = i + np.int32(dx + nx * (dy + ny * dz))
+                down = dx + 0.5 * dy + 0.25 * dz > 0
+                if values == "upwind" and down:
+                    take = rng.random(i.size) < 0.25
+                    i, j = i[take], j[take]
+                rows.append(i)
+                cols.append(j)
+                sign.append(np.full(i.size, 1.0 if down else -1.0))
+    rows = np.concatenate(rows + [np.arange(n, dtype=np.int32)])
+    cols = np.concatenate(cols + [np.arange(n, dtype=np.int32)])
+    order = np.argsort(cols.astype(np.int64) * n + rows, kind="stable")
+    colptr = np.zeros(n + 1, np.int64)
+    np.cumsum(np.bincount(cols, minlength=n), out=colptr[1:])
+    return rows, np.concatenate(sign), order, colptr, rows[order]
+
+
+def _values(case, dims, seed, index):
+    """Row-dominant values in CSC order: convection -1 +- 0.3 with a jitter,
+    random couplings in [-1, 0] with a perturbation, or the complex form of the
+    latter (couplings w (1 + i eps), diagonal shifted by 0.5 i)."""
+    rows, sign, order, colptr, _ = _pattern(dims, case["stencil"], case["values"])
+    rng = np.random.default_rng([seed, index])
+    n, m = colptr.size - 1, sign.size
+    if case["values"] in ("convection", "upwind"):
+        off = -1.0 + 0.3 * sign + rng.uniform(-0.05, 0.05, m)
+        shift = 0.1
+    elif case["values"] == "random":
+        off = rng.uniform(-1.0, 0.0, m) + rng.uniform(-0.15, 0.15, m)
+        shift = 0.1
+    else:
+        off = rng.uniform(-1.0, 0.0, m) * (1 + 1j * rng.uniform(-0.2, 0.2, m))
+        shift = 0.05 + 0.5j
+    diag = np.bincount(rows[:m], np.abs(off), minlength=n) + shift
+    return np.concatenate([off, diag])[order]
+
+
+def _handle(case, dims):
+    _, _, _, colptr, rowind = _pattern(dims, case["stencil"], case["values"])
+    return SelInv(colptr.size - 1, colptr, rowind, _order(dims, case["leaf"]), max_super=case["cap"],
+                  relax=case["leaf"], pad_pct=case["pad_pct"],
+                  symbolic="exact" if case["values"] == "upwind" else "symmetrized",
+                  complex_values=case["values"] == "complex")
+
+
+# ---------------------------------------------------------------------------
+# a pass
+# ---------------------------------------------------------------------------
+
+def prepare(case, seed):
+    mats, vals, outs = [], [], []
+    for k, dims in enumerate(_grids(case)):
+        h = _handle(case, dims)
+        v = torch.from_numpy(_values(case, dims, seed, k)).cuda()
+        h.factor_device(v)
+        mats.append(h)
+        vals.append(v)
+        outs.append(torch.empty_like(v))
+    batch = Batch(mats) if len(mats) > 1 else None
+    torch.cuda.current_stream().synchronize()  # the passes run on a stream of their own, as graphs need
+    return {"case": case, "mats": mats, "vals": vals, "outs": outs, "batch": batch, "stream": torch.cuda.Stream()}
+
+
+def run(state):
+    c, st = state["case"], state["stream"]
+    if state["batch"] is not None:
+        state["batch"].run(c["precision"], stream=st, graph=c["graph"])
+        for h, out in zip(state["mats"], state["outs"]):
+            h.get_selected_device(out, stream=st)
+        return state["outs"]
+    h, out = state["mats"][0], state["outs"][0]
+    if c["refactor"]:
+        h.factor_device(state["vals"][0], stream=st)
+    h.run(c["precision"], stream=st, graph=c["graph"])
+    return h.get_selected_device(out, stream=st)
+
+
+@functools.lru_cache(maxsize=32)
+def _work(dims, stencil, values, cap, leaf, pad_pct, refactor, elem):
+    h = _handle({"stencil": stencil, "values": values, "cap": cap, "leaf": leaf, "pad_pct": pad_pct}, dims)
+    st = h.structure()
+    s = np.diff(st["xsup"]).astype(float)
+    cl, cu = np.diff(st["rl_ptr"]).astype(float), np.diff(st["ru_ptr"]).astype(float)
+    # the products on 2x2 real blocks of one complex entry need half of the real form's flops
+    half = 0.5 if values == "complex" else 1.0
+    flops = half * float((4 * s * cl * cu + 2 * s * s * cu + s * s * (cl + cu) + 4 / 3 * s ** 3).sum())
+    panels, diag = float((s * (cl + cu)).sum()), float((s * s).sum())
+    # the inverse's blocks written and its selected entries delivered
+    nbytes = panels * elem + diag * 8 + 8 * float(h.nnz)
+    if refactor:  # from the values; the factors are intermediate
+        flops += half * float((2 / 3 * s ** 3 + s * s * (cl + cu) + 2 * s * cl * cu).sum())
+        nbytes += 8 * float(h.nnz)
+    else:
+        nbytes += 8 * (panels + diag)
+    h.close()
+    return nbytes * half if values == "complex" else nbytes, flops
+
+
+def work(case):
+    elem = 8 if case["precision"] == "fp64" else 4
+    tot = np.zeros(2)
+    for dims in _grids(case):
+        tot += _work(dims, case["stencil"], case["values"], case["cap"], case["leaf"], case["pad_pct"],
+                     case["refactor"], elem)
+    return {"bytes": float(tot[0]), "flops": float(tot[1])}
+
+
+# ---------------------------------------------------------------------------
+# the same entries from the definition, in 64 bits
+# ---------------------------------------------------------------------------
+
+def _inverse(m):
+    """Inverse of a dense matrix with a dominant diagonal, by 2x2 block elimination."""
+    n = m.shape[0]
+    if n <= 512:
+        return torch.linalg.inv(m)
+    h = n // 2
+    ai = _inverse(m[:h, :h].contiguous())
+    b, c = m[:h, h:].contiguous(), m[h:, :h].contiguous()
+    aib = ai @ b
+    si = _inverse(m[h:, h:] - c @ aib)
+    cai = c @ ai
+    x12 = -(aib @ si)
+    return torch.cat([torch.cat([ai - x12 @ cai, x12], 1), torch.cat([-(si @ cai), si], 1)], 0)
+
+
+def _exact(case, dims, seed, index):
+    """Selected inverse by block elimination along the last axis: the matrix is
+    block tridiagonal in its grid lines (planes), forward over the Schur
+    complements, backward over the diagonal and neighbour blocks of the inverse."""
+    rows, _, order, colptr, rowind = _pattern(dims, case["stencil"], case["values"])
+    dev = torch.device("cuda" if torch.cuda.is_available() else "cpu")
+    nb = dims[-1]
+    bs = (colptr.size - 1) // nb
+    v = torch.from_numpy(_values(case, dims, seed, index)).to(dev)
+    r = torch.from_numpy(rowind.astype(np.int64)).to(dev)
+    c = torch.from_numpy(np.repeat(np.arange(colptr.size - 1), np.diff(colptr))).to(dev)
+    rb, cb = r // bs, c // bs
+
+    def block(i, j):
+        p = torch.nonzero((rb == i) & (cb == j)).flatten()
+        b = torch.zeros(bs, bs, dtype=v.dtype, device=dev)
+        b[r[p] % bs, c[p] % bs] = v[p]
+        return b, p
+
+    low, up, sinv, where = [None] * nb, [None] * nb, [None] * nb, {}
+    for k in range(nb):
+        s, where[k, k] = block(k, k)
+        if k:
+            low[k], where[k, k - 1] = block(k, k - 1)
+            up[k - 1], where[k - 1, k] = block(k - 1, k)
+            s = s - low[k] @ (sinv[k - 1] @ up[k - 1])
+        sinv[k] = _inverse(s)
+    out = torch.zeros_like(v)
+
+    def take(x, i, j):
+        # x = A^{-1} block (i, j) holds out[p] = A^{-1}(col, row) of the entries p of block (j, i)
+        p = where[j, i]
+        out[p] = x[c[p] % bs, r[p] % bs]
+
+    x = sinv[nb - 1]
+    take(x, nb - 1, nb - 1)
+    for k in range(nb - 2, -1, -1):
+        su, ls = sinv[k] @ up[k], low[k + 1] @ sinv[k]
+        xu = -(su @ x)
+        take(xu, k, k + 1)
+        take(-(x @ ls), k + 1, k)
+        x = sinv[k] - xu @ ls
+        take(x, k, k)
+    return out
+
+
+def exact(case, seed):
+    out = [_exact(case, dims, seed, k) for k, dims in enumerate(_grids(case))]
+    return out if len(out) > 1 else out[0]
