@@ -14,7 +14,8 @@ A case is a dict of
   stencil     "star" (5/7 points) or "box" (9/27 points)
   values      "convection", "random", "upwind" (non-symmetric pattern, exact
               analysis) or "complex"
-  cap, leaf, pad_pct   supernode partition rules
+  cap, leaf, pad_pct   supernode partition rules (complex: cap counts the real
+              form's columns, two per node; leaf counts nodes)
   precision   "fp64", "mixed_fp32" or "mixed_bf16x3"
   refactor    whether a pass starts from new values in device memory
   graph       whether the sweep is replayed from a HIP graph
@@ -53,7 +54,7 @@ def listed():
         # structurally non-symmetric pattern, analysed exactly (R_L != R_U)
         _case("256x256", "box", "upwind", 128, name="upwind_256_exact"),
         # complex shifted operator, held in its real form
-        _case("256x256", "box", "complex", 256, leaf=128, name="complex_256_fp64"),
+        _case("256x256", "box", "complex", 256, name="complex_256_fp64"),
         # 3D convection-diffusion
         _case("48x48x48", "star", "convection", 256, name="grid3d_48_fp64"),
         # a ragged 3D box in mixed FP32, eager launches
@@ -89,7 +90,7 @@ def draw(rng):
     if kind == "upwind":
         return _case(dims, stencil, "upwind", rng.randint(48, 160), prec, graph=graph)
     if kind == "complex":
-        return _case(dims, stencil, "complex", 2 * rng.randint(24, 128), prec, leaf=128, refactor=refactor,
+        return _case(dims, stencil, "complex", 2 * rng.randint(24, 128), prec, refactor=refactor,
                      graph=graph)
     return _case(dims, stencil, values, rng.randint(24, 160), prec, leaf=rng.choice([16, 32, 64]),
                  refactor=refactor, graph=graph)
@@ -184,7 +185,7 @@ def _values(case, dims, seed, index):
 def _handle(case, dims):
     _, _, _, colptr, rowind = _pattern(dims, case["stencil"], case["values"])
     return SelInv(colptr.size - 1, colptr, rowind, _order(dims, case["leaf"]), max_super=case["cap"],
-                  relax=case["leaf"], pad_pct=case["pad_pct"],
+                  relax=case["leaf"] * (2 if case["values"] == "complex" else 1), pad_pct=case["pad_pct"],
                   symbolic="exact" if case["values"] == "upwind" else "symmetrized",
                   complex_values=case["values"] == "complex")
 
