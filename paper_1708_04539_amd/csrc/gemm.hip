@@ -45,19 +45,38 @@ __device__ __forceinline__ int xcd_tile(int b, int n) {
     return x * q + min(x, r) + i;
 }
 
-// Occupancy: four workgroups per compute unit for the 32- and 64-wide tiles
-// (their LDS allows four; at most 128 VGPRs, which the two chunks in flight
-// of the FP64 64-wide tile would otherwise exceed), two for the 128-wide ones.
+// LDS stages of the tiles that load straight into LDS
+template <int MODE, int BM>
+struct DmaStages {
+    static constexpr int value = 2;
+};
+// Tiles of a product that take gemm_tile_dma: operands in the arithmetic's
+// own type, 64 wide (FP32 also 128 wide; 128-wide FP64 tiles leave it no
+// registers).  The 32-wide tiles serve launches that wait for their loads, not
+// for the matrix pipe.
+template <int MODE, int BM, typename TA>
+constexpr bool kDmaTile = (BM == 64 || (BM == 128 && MODE == CMP_F32)) && MODE != CMP_BF16X3 && std::is_same<TA, typename Mode<MODE>::T>::value;
+
+// Occupancy: at least four workgroups per compute unit for the 32- and
+// 64-wide tiles (at most 128 VGPRs), two for the 128-wide ones.
 template <int MODE, int BM, int BN, typename TA, typename TC, int ROLE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BM == 128 ? 2 : 4))) void gemm_v2(const GemmProb *__restrict__ probs,
                                                const GemmTile *__restrict__ tiles) {
-    __shared__ Smem<MODE, BM, BN> sm;
+    constexpr bool D = kDmaTile<MODE, BM, TA>;
+    typedef std::conditional_t<D, DmaSmem<BM, BN, DmaStages<MODE, BM>::value>, Smem<MODE, BM, BN>> SM;
+    __shared__ SM sm;
     const GemmTile tl = tiles[xcd_tile(blockIdx.x, gridDim.x)];
     // only the step-4 product accumulates into an input matrix
-    gemm_tile<MODE, BM, BN, TA, TC, ROLE == 2>(probs[tl.prob], tl.m0, tl.n0, sm);
+    auto tile = [&](int n0) __attribute__((always_inline)) {
+        if constexpr (D)
+            gemm_tile_dma<MODE, BM, BN, DmaStages<MODE, BM>::value, TC, ROLE == 2>(probs[tl.prob], tl.m0, n0, sm);
+        else
+            gemm_tile<MODE, BM, BN, TA, TC, ROLE == 2>(probs[tl.prob], tl.m0, n0, sm);
+    };
+    tile(tl.n0);
     if (tl.n1 > 0) {
         __syncthreads();  // LDS free for the second tile
-        gemm_tile<MODE, BM, BN, TA, TC, ROLE == 2>(probs[tl.prob], tl.m0, tl.n1 - 1, sm);
+        tile(tl.n1 - 1);
     }
 }
 
@@ -117,15 +136,20 @@ __global__ __launch_bounds__(256) void step4_gather(const GemmProb *__restrict__
                                                     const GemmTile *__restrict__ tiles, int ntiles,
                                                     const MatDev *__restrict__ mats,
                                                     const GatherTile *__restrict__ gtiles) {
+    constexpr bool D = kDmaTile<MODE, BM, TA>;
     union Shared {
-        Smem<MODE, BM, BN> g;
+        std::conditional_t<D, DmaSmem<BM, BN, DmaStages<MODE, BM>::value>, Smem<MODE, BM, BN>> g;
         GatherSmem<TA> t;
     };
     __shared__ Shared sm;
     const int b = blockIdx.x;
     if (b < ntiles) {
         const GemmTile tl = tiles[xcd_tile(b, ntiles)];
-        gemm_tile<MODE, BM, BN, TA, double, true, true>(probs[tl.prob], tl.m0, tl.n0, sm.g, mats);
+        if constexpr (D)
+            gemm_tile_dma<MODE, BM, BN, DmaStages<MODE, BM>::value, double, true, true>(probs[tl.prob], tl.m0, tl.n0,
+                                                                                       sm.g, mats);
+        else
+            gemm_tile<MODE, BM, BN, TA, double, true, true>(probs[tl.prob], tl.m0, tl.n0, sm.g, mats);
     } else {
         const GatherTile gt = gtiles[b - ntiles];
         gather_tile<TA>(mats[gt.mat], gt, sm.t);

@@ -33,6 +33,11 @@ using namespace selinv;
 
 namespace {
 
+// Bytes past the end of every allocation that a kernel may read: the loads
+// that write LDS (tiles.hpp, DmaOperand) move 16 bytes at a time, and the last
+// one of an operand may start at its last element.
+constexpr size_t kReadSlack = 16;
+
 // Source of device memory (selinv_set_allocator): hipMalloc / hipFree, or the
 // caller's hook.  Each handle and batch keeps the source in effect when it was
 // created and returns every allocation to it.  Memory handed back to a hook
@@ -43,7 +48,7 @@ struct DevAlloc {
     selinv_free_fn dealloc = nullptr;
     void *ctx = nullptr;
     hipError_t get(void **p, size_t bytes) const {
-        bytes = std::max<size_t>(bytes, 16);
+        bytes += kReadSlack;
         if (!alloc) return hipMalloc(p, bytes);
         *p = alloc(bytes, ctx);
         if (!*p) return hipErrorOutOfMemory;
@@ -373,6 +378,9 @@ constexpr int kSplitWidth = 64;
 constexpr double kSplitKBelow = 512;
 constexpr int kSplitKMin = 512;
 constexpr double kTile128From = 192;
+// leading dimensions up to which the 64- and 128-wide tiles address their
+// operands (tiles.hpp, DmaOperand: offsets inside one load below 2^32 bytes)
+constexpr int kDmaMaxLd = 1 << 26;
 
 // row-block major: the tiles of one strip of op(A) are neighbours in the
 // list (the GEMM kernel keeps neighbours on one XCD).  pair: a product whose
@@ -439,14 +447,18 @@ void order_by_k_length(const std::vector<GemmProb> &probs, std::vector<GemmTile>
 void emit_launch(const std::vector<GemmProb> &probs, size_t first, std::vector<GemmTile> &tiles, Range &r,
                  bool allow128 = false, int forced = 0, bool pair_lower = false) {
     double area = 0, t128 = 0, t64 = 0;
+    int ld_max = 0;
     for (size_t q = first; q < probs.size(); q++) {
         const double M = probs[q].M, N = probs[q].N;
+        ld_max = std::max({ld_max, probs[q].lda, probs[q].ldb});
         area += M * N;
         t128 += std::ceil(M / 128) * std::ceil(N / 128);
         t64 += std::ceil(M / 64) * std::ceil(N / 64);
     }
     r.tile = GEMM_TILE_64;
-    if (forced == GEMM_TILE_32 || forced == GEMM_TILE_64 || forced == GEMM_TILE_128)
+    if (ld_max > kDmaMaxLd)
+        r.tile = GEMM_TILE_32;  // 64-bit addresses per element
+    else if (forced == GEMM_TILE_32 || forced == GEMM_TILE_64 || forced == GEMM_TILE_128)
         r.tile = forced;  // a measured choice (selinv_tune)
     else if (t64 < kTile32Below)
         r.tile = GEMM_TILE_32;
@@ -1947,6 +1959,9 @@ static selinv_status build_lu(selinv_handle h) {
                 double *D = D0 + r.off_d;
                 const int64_t tile = j0 + j0 * ld;
                 inside(r.off_d + tile, (b - 1) + (b - 1) * ld, r.off_d, ss);
+                // the L and U panels are row-contiguous operands: at most one
+                // leading dimension inside a load
+                if (std::max(cl, cu) >= 1 << 29) ok = false;
                 lus.push_back(LuTile{D, s, j0, r.f, 0});
                 TriItem ti{};
                 ti.D = D;

@@ -228,6 +228,112 @@ struct SplitMRows {
     }
 };
 
+// Results of one output tile: C = alpha acc + beta Cin from the accumulators
+// of the workgroup's wavefronts (each a (BM/2) x (BN/2) block of 16x16 MFMA
+// results), the odd columns of complex blocks, and the push into the
+// children's G.
+template <int MODE, int BM, int BN, typename TC, bool CIN, bool PUSH, typename TG, typename Acc>
+__device__ __forceinline__ void gemm_store(const GemmProb &p, const int m0, const int n0,
+                                           Acc (&acc)[BM / 32][BN / 32], const MatDev *mats) {
+    constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int M = p.M, N = p.N;
+    SELINV_GLOBAL TC *__restrict__ C = gptr_w((TC *)p.C);
+    const SELINV_GLOBAL TC *__restrict__ Cin = gptr((const TC *)p.Cin);
+    const int64_t ldc = p.ldc, ldcin = p.ldcin;
+    const double alpha = p.alpha, beta = p.beta;
+    // rows of the 16x16 result held by this lane: v_mfma_f64_16x16x4
+    // interleaves the four row groups (row = lane/16 + 4v); the f32 and bf16
+    // forms keep them contiguous (row = 4 (lane/16) + v)
+    auto row_n = [&](int j, int v) {
+        const int nr = (MODE == CMP_F64) ? (lane >> 4) + 4 * v : 4 * (lane >> 4) + v;
+        return n0 + wn * WN + j * 16 + nr;
+    };
+    const bool has_cin = CIN && p.Cin != nullptr;
+    // The Cin loads of CR rows of 16x16 tiles in flight together (clamped
+    // addresses): every row of the wavefront's tiles up to 16 values per lane
+    // (Cin is C itself in step 4, so later loads cannot pass the stores)
+    constexpr int CR = TM * TN <= 4 ? TM : 1;
+#pragma unroll
+    for (int i0 = 0; i0 < TM; i0 += CR) {
+        double cin[CR][TN][4];
+        if (has_cin) {
+#pragma unroll
+            for (int ii = 0; ii < CR; ii++)
+#pragma unroll
+                for (int j = 0; j < TN; j++)
+#pragma unroll
+                    for (int v = 0; v < 4; v++) {
+                        const int64_t gm = min(m0 + wm * WM + (i0 + ii) * 16 + (lane & 15), M - 1);
+                        const int64_t gn = min(row_n(j, v), N - 1);
+                        cin[ii][j][v] = (double)Cin[gm + gn * ldcin];
+                    }
+        }
+#pragma unroll
+        for (int ii = 0; ii < CR; ii++) {
+            const int i = i0 + ii;
+            const int gm = m0 + wm * WM + i * 16 + (lane & 15);
+            if (gm >= M) continue;
+            // complex blocks: the entry of the odd column that this one gives
+            const double csign = (gm & 1) ? -1.0 : 1.0;
+#pragma unroll
+            for (int j = 0; j < TN; j++)
+#pragma unroll
+                for (int v = 0; v < 4; v++) {
+                    const int gn = row_n(j, v);
+                    if (gn >= N) continue;
+                    double r = alpha * (double)acc[i][j][v];
+                    if (has_cin) r += beta * cin[ii][j][v];
+                    C[gm + (int64_t)gn * ldc] = (TC)r;
+                    if (p.cpx) C[(gm ^ 1) + (int64_t)gn * ldc + ldc / 2] = (TC)(csign * r);
+                    if constexpr (PUSH) acc[i][j][v] = (TC)r;  // the stored value, for the push below
+                }
+        }
+    }
+    if constexpr (PUSH) {
+        if (p.push_sn >= 0) {
+            const MatDev &Md = mats[p.push_mat];
+            const SELINV_GLOBAL SnRec *sn = gptr(Md.sn);
+            const SELINV_GLOBAL int32_t *kp = gptr(Md.kids_ptr);
+            const SELINV_GLOBAL int32_t *kids = gptr(Md.kids);
+            const int P = p.push_sn, sP = M;  // A^{-T}(P,P) is M x M
+            const int q1 = kp[P + 1];
+            for (int q = kp[P]; q < q1; q++) {
+                const int32_t K = kids[q];
+                const SELINV_GLOBAL int32_t *posL = gptr(Md.push_pos) + gptr(Md.push_off)[K];
+                const SELINV_GLOBAL int32_t *posU = posL + sP;
+                const int64_t clK = sn[K].cl;
+                SELINV_GLOBAL TG *G = gptr_w((TG *)Md.G) + sn[K].g_off;
+#pragma unroll
+                for (int i = 0; i < TM; i++) {
+                    const int gm = m0 + wm * WM + i * 16 + (lane & 15);
+                    if (gm >= M) continue;
+                    const int a = posL[gm];
+                    // complex blocks: column gn of the problem is column 2 gn
+                    // of A^{-T}(P,P), and it gives entry (gm ^ 1, 2 gn + 1)
+                    const int a1 = p.cpx ? posL[gm ^ 1] : -1;
+                    const TG csign = (gm & 1) ? (TG)-1 : (TG)1;
+#pragma unroll
+                    for (int j = 0; j < TN; j++)
+#pragma unroll
+                        for (int v = 0; v < 4; v++) {
+                            const int gn = row_n(j, v);
+                            if (gn >= N) continue;
+                            const int c = p.cpx ? 2 * gn : gn;
+                            const int b = posU[c];
+                            if (a >= 0 && b >= 0) G[a + b * clK] = (TG)acc[i][j][v];
+                            if (p.cpx) {
+                                const int b1 = posU[c + 1];
+                                if (a1 >= 0 && b1 >= 0) G[a1 + b1 * clK] = csign * (TG)acc[i][j][v];
+                            }
+                        }
+                }
+            }
+        }
+    }
+}
+
 // One BM x BN output tile of C = alpha op(A) op(B) + beta Cin, computed by
 // the 256 threads of the calling workgroup (see gemm.hip for the design),
 // for fixed operand forms OPA, OPB (0: N, 1: T).
@@ -357,12 +463,11 @@ __device__ __forceinline__ void gemm_tile_op(const GemmProb &p, const int m0, co
     // Register slots of the chunks loaded ahead of their LDS stage: PF = 2
     // for the 32-wide tiles, which serve the launches that cannot fill the
     // device, where each workgroup waits on the latency of every chunk's
-    // loads (two chunks in flight halve that wait), and for the FP64 64-wide
-    // products (within 128 VGPRs, see gemm.hip); 1 for the other tiles, whose
+    // loads (two chunks in flight halve that wait); 1 for the other tiles, whose
     // launches hide it behind other workgroups (and whose registers would
     // cost occupancy; measured: two slots on the 128-wide split-BF16
     // steps-3/5 tile left C4 at 15.9 ms).
-    constexpr int PF = (BM == 32 || (MODE == CMP_F64 && BM == 64 && !GA && !PUSH)) ? 2 : 1;
+    constexpr int PF = BM == 32 ? 2 : 1;
     TA ra[PF][VA ? 1 : LA], rb[PF][VB ? 1 : LB];
     typename VecA::Regs rva[PF];
     typename VecB::Regs rvb[PF];
@@ -549,99 +654,7 @@ __device__ __forceinline__ void gemm_tile_op(const GemmProb &p, const int m0, co
         }
     }
 
-    SELINV_GLOBAL TC *__restrict__ C = gptr_w((TC *)p.C);
-    const SELINV_GLOBAL TC *__restrict__ Cin = gptr((const TC *)p.Cin);
-    const int64_t ldc = p.ldc, ldcin = p.ldcin;
-    const double alpha = p.alpha, beta = p.beta;
-    // rows of the 16x16 result held by this lane: v_mfma_f64_16x16x4
-    // interleaves the four row groups (row = lane/16 + 4v); the f32 and bf16
-    // forms keep them contiguous (row = 4 (lane/16) + v)
-    auto row_n = [&](int j, int v) {
-        const int nr = (MODE == CMP_F64) ? (lane >> 4) + 4 * v : 4 * (lane >> 4) + v;
-        return n0 + wn * WN + j * 16 + nr;
-    };
-    const bool has_cin = CIN && p.Cin != nullptr;
-    // The Cin loads of CR rows of 16x16 tiles in flight together (clamped
-    // addresses): every row of the wavefront's tiles up to 16 values per lane
-    // (Cin is C itself in step 4, so later loads cannot pass the stores)
-    constexpr int CR = TM * TN <= 4 ? TM : 1;
-#pragma unroll
-    for (int i0 = 0; i0 < TM; i0 += CR) {
-        double cin[CR][TN][4];
-        if (has_cin) {
-#pragma unroll
-            for (int ii = 0; ii < CR; ii++)
-#pragma unroll
-                for (int j = 0; j < TN; j++)
-#pragma unroll
-                    for (int v = 0; v < 4; v++) {
-                        const int64_t gm = min(m0 + wm * WM + (i0 + ii) * 16 + (lane & 15), M - 1);
-                        const int64_t gn = min(row_n(j, v), N - 1);
-                        cin[ii][j][v] = (double)Cin[gm + gn * ldcin];
-                    }
-        }
-#pragma unroll
-        for (int ii = 0; ii < CR; ii++) {
-            const int i = i0 + ii;
-            const int gm = m0 + wm * WM + i * 16 + (lane & 15);
-            if (gm >= M) continue;
-            // complex blocks: the entry of the odd column that this one gives
-            const double csign = (gm & 1) ? -1.0 : 1.0;
-#pragma unroll
-            for (int j = 0; j < TN; j++)
-#pragma unroll
-                for (int v = 0; v < 4; v++) {
-                    const int gn = row_n(j, v);
-                    if (gn >= N) continue;
-                    double r = alpha * (double)acc[i][j][v];
-                    if (has_cin) r += beta * cin[ii][j][v];
-                    C[gm + (int64_t)gn * ldc] = (TC)r;
-                    if (p.cpx) C[(gm ^ 1) + (int64_t)gn * ldc + ldc / 2] = (TC)(csign * r);
-                    if constexpr (PUSH) acc[i][j][v] = (TC)r;  // the stored value, for the push below
-                }
-        }
-    }
-    if constexpr (PUSH) {
-        if (p.push_sn >= 0) {
-            const MatDev &Md = mats[p.push_mat];
-            const SELINV_GLOBAL SnRec *sn = gptr(Md.sn);
-            const SELINV_GLOBAL int32_t *kp = gptr(Md.kids_ptr);
-            const SELINV_GLOBAL int32_t *kids = gptr(Md.kids);
-            const int P = p.push_sn, sP = M;  // A^{-T}(P,P) is M x M
-            const int q1 = kp[P + 1];
-            for (int q = kp[P]; q < q1; q++) {
-                const int32_t K = kids[q];
-                const SELINV_GLOBAL int32_t *posL = gptr(Md.push_pos) + gptr(Md.push_off)[K];
-                const SELINV_GLOBAL int32_t *posU = posL + sP;
-                const int64_t clK = sn[K].cl;
-                SELINV_GLOBAL TG *G = gptr_w((TG *)Md.G) + sn[K].g_off;
-#pragma unroll
-                for (int i = 0; i < TM; i++) {
-                    const int gm = m0 + wm * WM + i * 16 + (lane & 15);
-                    if (gm >= M) continue;
-                    const int a = posL[gm];
-                    // complex blocks: column gn of the problem is column 2 gn
-                    // of A^{-T}(P,P), and it gives entry (gm ^ 1, 2 gn + 1)
-                    const int a1 = p.cpx ? posL[gm ^ 1] : -1;
-                    const TG csign = (gm & 1) ? (TG)-1 : (TG)1;
-#pragma unroll
-                    for (int j = 0; j < TN; j++)
-#pragma unroll
-                        for (int v = 0; v < 4; v++) {
-                            const int gn = row_n(j, v);
-                            if (gn >= N) continue;
-                            const int c = p.cpx ? 2 * gn : gn;
-                            const int b = posU[c];
-                            if (a >= 0 && b >= 0) G[a + b * clK] = (TG)acc[i][j][v];
-                            if (p.cpx) {
-                                const int b1 = posU[c + 1];
-                                if (a1 >= 0 && b1 >= 0) G[a1 + b1 * clK] = csign * (TG)acc[i][j][v];
-                            }
-                        }
-                }
-            }
-        }
-    }
+    gemm_store<MODE, BM, BN, TC, CIN, PUSH, TG>(p, m0, n0, acc, mats);
 }
 
 // Dispatch on the operand forms of the problem (uniform across the
@@ -673,6 +686,248 @@ __device__ __forceinline__ void gemm_tile_g35(const GemmProb &p, const int m0, c
         gemm_tile_op<MODE, BM, BN, TA, TA, false, BK, 0, 0, false, TA, true>(p, m0, n0, sm, mats);
     else
         gemm_tile_op<MODE, BM, BN, TA, TA, false, BK, 1, 0, false, TA, true>(p, m0, n0, sm, mats);
+}
+
+// ---------------------------------------------------------------------------
+// Product tiles whose operands go from memory straight into LDS
+// ---------------------------------------------------------------------------
+// The FP64 and FP32 products of 64-wide tiles (and the FP32 ones of 128-wide
+// tiles), for operands stored in the arithmetic's own type.  What bound the
+// register-staged tile there was not the matrix pipe but the vector
+// instructions beside it: v_mfma_f64 does not run beside other VALU work of
+// its SIMD (SQ_VALU_MFMA_COEXEC_CYCLES 0), and every staged element cost three
+// of them (a 64-bit address, the select of the LDS store), 1.5 per MFMA.  Here
+// a chunk is moved by buffer loads that write LDS themselves: the chunk is a
+// scalar offset, the lane's offset a constant register, and the k loop holds
+// MFMAs and LDS reads only.  Measured on the steps-3/5 launches of the 3D 64^3
+// 27-point matrix (1.64 TFLOP): FP64 29.9 -> 25.3 ms (65 TFLOP/s, MFMA busy
+// 78 -> 92 % of the SIMD cycles), FP32 17.3 -> 12.9 ms (127 TFLOP/s).  A third
+// stage (three workgroups per compute unit instead of five) 28.6 ms where two
+// took 27.8 ms; 128-wide FP64 tiles (two workgroups per compute unit, a
+// quarter of the tiles to balance) 33.5 ms.
+//
+// A chunk is 128 bytes of k (16 FP64, 32 FP32) of every row of op(A) and
+// column of op(B); one wavefront-wide load moves 1 KB.  The load writes lane
+// l's 16 bytes at l * 16, so the layout is swizzled on the source side, in
+// units of 16 bytes, to spread the MFMA operand reads over the banks:
+//   contiguous along k (A with op = T, B with op = N): row r holds its 128
+//     bytes at r * 128, unit u at place u ^ ((r >> 1) & 7);
+//   contiguous along the rows: row k of the chunk holds its R elements at
+//     k * R * E, byte m * E at (m * E) ^ ((k & 3) * 16 E): the four k of an
+//     operand read fall on different bank groups.
+// ST LDS stages: chunk c + ST - 1 is issued after the barrier that ends chunk
+// c - 1, one barrier per chunk.  Rows past the operand are read as its last
+// row (k-contiguous) or as whatever follows them, zeros past the operand's end
+// (the buffer's range); they only reach results that are not stored.  The k
+// past the operand in the last chunk are cleared in LDS before they are used,
+// up to the next multiple of 4; the MFMAs beyond are left out.  The products
+// are those of the register-staged tile in the same order, so the results are
+// equal bit for bit.
+template <int BM, int BN, int ST>
+struct DmaSmem {
+    alignas(128) char b[ST][(BM + BN) * 128];
+};
+
+typedef __attribute__((address_space(3))) char lds_char;
+
+// One operand of such a tile: R rows (columns of op(B)) from r0 on; KC:
+// contiguous along k.
+template <typename T, int R, bool KC>
+struct DmaOperand {
+    static constexpr int E = sizeof(T), BK = 128 / E, NI = R / 32, RB = R * E;
+    const char *base;   // r0, k = 0
+    int64_t size;       // bytes from base to the operand's end, and to the end of its last 16-byte unit
+    int64_t kstep;      // bytes per chunk
+    int64_t rstep;      // bytes between two rows (KC) or two k
+    bool wide;          // offsets from base do not fit 32 bits (uniform)
+    uint32_t voff[NI];  // this lane's offset from base; wide: from the load's first row or k
+    int lim;            // rows past the operand read its last one, r0 + lim
+    // rows (KC) or k of one load
+    static constexpr int PER = KC ? 8 : 1024 / RB;
+    __device__ __forceinline__ void init(const void *ptr, int64_t ld, int r0, int rows, int K, int lane, int wave) {
+        base = (const char *)ptr + (KC ? (int64_t)r0 * ld : (int64_t)r0) * E;
+        lim = rows - 1 - r0;
+        size = ((KC ? (int64_t)lim * ld + K : (int64_t)(K - 1) * ld + (lim + 1)) * E) + (16 - E);
+        kstep = KC ? 128 : BK * ld * E;
+        rstep = ld * E;
+        wide = size > 0x7fffffff || (int64_t)R * ld * E > 0x7fffffff;
+#pragma unroll
+        for (int i = 0; i < NI; i++) {
+            const int q = wave * NI + i;
+            const int first = wide ? (KC ? min(q * PER, lim) : q * PER) : 0;
+            if constexpr (KC) {
+                const int r = q * 8 + (lane >> 3), u = (lane & 7) ^ ((r >> 1) & 7);
+                voff[i] = (uint32_t)(min(r, lim) - first) * (uint32_t)rstep + u * 16;
+            } else {
+                const int pos = lane * 16, k = q * PER + pos / RB;
+                voff[i] = (uint32_t)(k - first) * (uint32_t)rstep + ((pos % RB) ^ (((k & 3) * 16 * E) & (RB - 1)));
+            }
+        }
+    }
+    __device__ __forceinline__ void issue(lds_char *lds, int c, int wave) const {
+        if (!wide) {
+            // one descriptor, the chunk in the scalar offset
+            const __amdgpu_buffer_rsrc_t rs =
+                __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)size, 0x00020000);
+            const int so = c * (int)kstep;
+#pragma unroll
+            for (int i = 0; i < NI; i++)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    rs, (__attribute__((address_space(3))) void *)(lds + (wave * NI + i) * 1024), 16, voff[i], so, 0, 0);
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < NI; i++) {
+            const int q = wave * NI + i;
+            const int64_t off = c * kstep + (KC ? min(q * PER, lim) : q * PER) * rstep, left = size - off;
+            const int32_t hi = (int32_t)(left >> 32);
+            const uint32_t num = hi < 0 ? 0u : hi > 0 ? 0xffffffffu : (uint32_t)left;
+            const __amdgpu_buffer_rsrc_t rs =
+                __builtin_amdgcn_make_buffer_rsrc((void *)(base + off), 0, (int)num, 0x00020000);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rs, (__attribute__((address_space(3))) void *)(lds + (wave * NI + i) * 1024), 16, voff[i], 0, 0, 0);
+        }
+    }
+    // byte offset of element (row r, k) of a chunk
+    static __device__ __forceinline__ int at(int r, int k) {
+        if constexpr (KC)
+            return r * 128 + (((k * E) / 16) ^ ((r >> 1) & 7)) * 16 + (k * E) % 16;
+        else
+            return k * RB + ((r * E) ^ (((k & 3) * 16 * E) & (RB - 1)));
+    }
+};
+
+// Waits for this wavefront's loads but the last N, and for every wavefront's.
+template <int N>
+__device__ __forceinline__ void dma_barrier() {
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+
+template <int MODE, int BM, int BN, int ST, typename TC, bool CIN, int OPA, int OPB, bool PUSH, typename TG>
+__device__ __forceinline__ void gemm_tile_dma_op(const GemmProb &p, const int m0, const int n0,
+                                                 DmaSmem<BM, BN, ST> &sm, const MatDev *mats) {
+    typedef typename Mode<MODE>::T T;
+    typedef typename Mode<MODE>::Acc Acc;
+    static_assert(MODE == CMP_F64 || MODE == CMP_F32, "operands in the arithmetic's own type");
+    static_assert(ST == 2 || ST == 3, "stages");
+    typedef DmaOperand<T, BM, OPA == 1> OA;
+    typedef DmaOperand<T, BN, OPB == 0> OB;
+    constexpr int E = sizeof(T), BK = OA::BK, WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave >> 1, wn = wave & 1, li = lane & 15, lk = lane >> 4;
+    const int K = p.K;
+    OA a;
+    OB b;
+    a.init(p.A, p.lda, m0, p.M, K, lane, wave);
+    b.init(p.B, p.ldb, n0, p.N, K, lane, wave);
+    lds_char *const lds = (lds_char *)&sm.b[0][0];
+    constexpr int SB = (BM + BN) * 128;  // bytes per stage
+    auto issue = [&](int c, int st) {
+        a.issue(lds + st * SB, c, wave);
+        b.issue(lds + st * SB + BM * 128, c, wave);
+    };
+    Acc acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+        for (int j = 0; j < TN; j++) acc[i][j] = Acc{0, 0, 0, 0};
+    // LDS offsets of this lane's operands (stage 0): of 16-row tile i at k
+    // step kk.  k-contiguous: the unit depends on kk, the tile is a constant
+    // further on; row-contiguous: the other way round.
+    constexpr int KS = BK / 4;
+    int oa[OPA == 1 ? KS : TM], ob[OPB == 0 ? KS : TN];
+#pragma unroll
+    for (int q = 0; q < (OPA == 1 ? KS : TM); q++)
+        oa[q] = OPA == 1 ? OA::at(wm * WM + li, 4 * q + lk) : OA::at(wm * WM + 16 * q + li, lk);
+#pragma unroll
+    for (int q = 0; q < (OPB == 0 ? KS : TN); q++)
+        ob[q] = BM * 128 + (OPB == 0 ? OB::at(wn * WN + li, 4 * q + lk) : OB::at(wn * WN + 16 * q + li, lk));
+    auto kstep = [&](int st, int q) {
+        T av[TM], bv[TN];
+#pragma unroll
+        for (int i = 0; i < TM; i++)
+            av[i] = *(const __attribute__((address_space(3))) T *)(lds + (OPA == 1 ? oa[q] : oa[i]) +
+                                                                   (st * SB + (OPA == 1 ? i * 16 * 128 : 4 * q * OA::RB)));
+#pragma unroll
+        for (int j = 0; j < TN; j++)
+            bv[j] = *(const __attribute__((address_space(3))) T *)(lds + (OPB == 0 ? ob[q] : ob[j]) +
+                                                                   (st * SB + (OPB == 0 ? j * 16 * 128 : 4 * q * OB::RB)));
+#pragma unroll
+        for (int i = 0; i < TM; i++)
+#pragma unroll
+            for (int j = 0; j < TN; j++) {
+                if constexpr (MODE == CMP_F64)
+                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(bv[j], av[i], acc[i][j], 0, 0, 0);
+                else
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[j], av[i], acc[i][j], 0, 0, 0);
+            }
+    };
+    // chunks whose products are all zero by the operands' triangular
+    // structure are skipped, as in gemm_tile_op
+    const int klo = max((p.ktri & 1) ? (p.cpx ? 2 * n0 : n0) : 0, (p.ktri & 2) ? m0 : 0);
+    const int nch = (K + BK - 1) / BK, nfull = K / BK, c0 = min(klo / BK, nch);
+    constexpr int NI = OA::NI + OB::NI;  // loads per wavefront and chunk
+    if (c0 < nch) issue(c0, 0);
+    if constexpr (ST == 3) {
+        if (c0 + 1 < nch) issue(c0 + 1, 1);
+    }
+    // chunk c (stage S) has landed everywhere and chunk c - 1 is used up
+    auto arrive = [&](int c, int S) {
+        if (ST == 3 && c + 1 < nch)
+            dma_barrier<(ST == 3 ? NI : 0)>();
+        else
+            dma_barrier<0>();
+        if (c + ST - 1 < nch) issue(c + ST - 1, (S + ST - 1) % ST);
+    };
+    auto step = [&](int c, auto S_) {
+        constexpr int S = decltype(S_)::value;
+        arrive(c, S);
+#pragma unroll
+        for (int q = 0; q < KS; q++) kstep(S, q);
+    };
+    typedef std::integral_constant<int, 0> S0;
+    typedef std::integral_constant<int, 1> S1;
+    typedef std::integral_constant<int, ST - 1> SL;
+    for (int c = c0; c < nfull; c += ST) {
+        step(c, S0{});
+        if (c + 1 < nfull) step(c + 1, S1{});
+        if constexpr (ST == 3) {
+            if (c + 2 < nfull) step(c + 2, SL{});
+        }
+    }
+    if (max(c0, nfull) < nch) {
+        // last, partial chunk
+        const int S = max(nfull - c0, 0) % ST;
+        arrive(nch - 1, S);
+        const int kr = K - nfull * BK, nz = (4 - (kr & 3)) & 3;
+        for (int e = threadIdx.x; e < nz * (BM + BN); e += 256) {
+            const int k = kr + e / (BM + BN), r = e % (BM + BN);
+            const int o = r < BM ? OA::at(r, k) : BM * 128 + OB::at(r - BM, k);
+            *(__attribute__((address_space(3))) T *)(lds + S * SB + o) = (T)0;
+        }
+        dma_barrier<0>();
+#pragma unroll
+        for (int q = 0; q < KS; q++)
+            if (4 * q < kr) kstep(S, q);
+    }
+    gemm_store<MODE, BM, BN, TC, CIN, PUSH, TG>(p, m0, n0, acc, mats);
+}
+
+template <int MODE, int BM, int BN, int ST, typename TC, bool CIN, bool PUSH = false>
+__device__ __forceinline__ void gemm_tile_dma(const GemmProb &p, const int m0, const int n0, DmaSmem<BM, BN, ST> &sm,
+                                              const MatDev *mats = nullptr) {
+    typedef typename Mode<MODE>::T TG;
+    if (p.opA == 0) {
+        if (p.opB == 0)
+            gemm_tile_dma_op<MODE, BM, BN, ST, TC, CIN, 0, 0, PUSH, TG>(p, m0, n0, sm, mats);
+        else
+            gemm_tile_dma_op<MODE, BM, BN, ST, TC, CIN, 0, 1, PUSH, TG>(p, m0, n0, sm, mats);
+    } else {
+        if (p.opB == 0)
+            gemm_tile_dma_op<MODE, BM, BN, ST, TC, CIN, 1, 0, PUSH, TG>(p, m0, n0, sm, mats);
+        else
+            gemm_tile_dma_op<MODE, BM, BN, ST, TC, CIN, 1, 1, PUSH, TG>(p, m0, n0, sm, mats);
+    }
 }
 
 // LDS of one gather tile

@@ -1,0 +1,74 @@
+"""Product tiles of the grouped GEMM at the sizes where they can go wrong:
+operands one short of, at and one past the edges of the tiles (64, 128) and of
+the k chunks (16, 32), down to single rows and columns.  Marked gpu.
+
+The 32-wide tiles stage their operands through registers; the wider FP64 and
+FP32 ones load them straight into LDS.  Every entry sums the same products in
+the same order in both, so the results are compared bit for bit, and with the
+oracle at the parity bar."""
+import numpy as np
+import pytest
+
+from oracle import Oracle
+from workloads import random_sparse
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"fp64": 1e-11, "mixed_fp32": 1e-5, "mixed_bf16x3": 1e-5}
+
+
+def table(levels, tile):
+    """Tuning table with one tile edge on every launch class, per-phase launches."""
+    return [4, levels, 1, tile, tile, tile, 0, 0] + [tile, tile, 1, 0] * levels
+
+
+def split_matrix(sizes, seed):
+    """Dense diagonal blocks of the given sizes, each coupled to all later
+    ones: supernode k has sizes[k] columns and c = sum(sizes[k+1:])."""
+    n = sum(sizes)
+    return random_sparse(n, 0.7, seed)
+
+
+# supernode widths from the first (deepest) to the root; c_L = c_U is the sum
+# of the widths that follow
+SIZES = [
+    (1, 1, 1),
+    (15, 16, 17, 1),
+    (31, 33, 32, 63),
+    (65, 63, 64, 1),
+    (64, 129, 127, 2),
+    (200, 3, 130, 61),
+]
+
+
+@pytest.mark.parametrize("sizes", SIZES, ids=["_".join(map(str, s)) for s in SIZES])
+@pytest.mark.parametrize("prec", ["fp64", "mixed_fp32", "mixed_bf16x3"])
+def test_tile_widths_agree(sizes, prec):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_1708_04539_amd import selinv as si
+    cap = max(sizes)
+    got = {}
+    for tile in (32, 64, 128):
+        # one matrix per supernode width as the cap, so that every width and
+        # every remainder of it occurs
+        for c in sorted(set(sizes)):
+            print("[case]", sizes, prec, "tile", tile, "cap", c, flush=True)
+            cp, ri, v, _ = split_matrix(sizes, 11)
+            s = si.SelInv(sum(sizes), cp, ri, None, c, 0, 100)
+            s.factor(v)
+            s.set_tuning(table(s.info["nlevels"], tile), prec)
+            s.run(prec)
+            r, col, x = s.export(sort=False)
+            if tile == 32:
+                o = Oracle(sum(sizes), cp, ri, None, c, 0, 0, 100).factor(v).selinv()
+                got[c] = x
+                r2, c2, ref = o.export()
+                k = np.lexsort((r, col))
+                assert np.array_equal(r[k], r2) and np.array_equal(col[k], c2)
+                assert np.abs(x[k] - ref).max() / np.abs(ref).max() <= TOL[prec]
+            else:
+                assert np.array_equal(x, got[c])
+            s.close()
+    assert cap in got
