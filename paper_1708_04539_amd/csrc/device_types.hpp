@@ -151,9 +151,10 @@ struct ReduceItem {
 };
 
 // device LU: one 64x64 diagonal tile (rows / columns j0 ..) of the s x s
-// block D of the supernode whose first column is f
+// block D of the supernode whose first column is f; the inverses of its
+// triangular factors go to the same place of Linv and Uinv
 struct LuTile {
-    double *D;
+    double *D, *Linv, *Uinv;
     int32_t s, j0, f, pad;
 };
 

@@ -16,6 +16,7 @@
 #include "device_types.hpp"
 #include "kernels.hpp"
 #include "tiles.hpp"
+#include "tri.hpp"
 
 namespace selinv {
 
@@ -27,19 +28,8 @@ namespace selinv {
 // wide) diagonal sub-block that starts at row/column o of one supernode's packed
 // L_KK \ U_KK (column-major, s x s; L unit lower, U upper).  A ragged
 // sub-block (s - o < 64) is padded with the identity, whose inverse stays the
-// identity and is not stored.  Blocked by 16:
-//   1. the 16x16 diagonal blocks, by substitution: wavefront w takes block w;
-//      lane c < 16 forms column c of (L_ww)^{-1} and lane 16 + c column c of
-//      (U_ww^T)^{-1} = row c of (U_ww)^{-1}, the same forward recurrence for
-//      both (the L diagonal is 1; U's diagonal enters through reciprocals
-//      formed once per block);
-//   2. the off-diagonal 16x16 blocks by distance d = 1, 2, 3 from the
-//      diagonal, on v_mfma_f64_16x16x4 (X = L^{-1}, Y = U^{-1}):
-//        X_ij = -X_ii (sum_{k=j}^{i-1} L_ik X_kj)      (i = j + d)
-//        Y_ij = -Y_ii (sum_{k=i+1}^{j} U_ik Y_kj)      (j = i + d)
-//      every block of one distance in parallel, one per wavefront.
-// Both results live packed in one LDS tile (strict lower part: L^{-1}; upper
-// part with the diagonal: U^{-1}) and are written out with coalesced stores,
+// identity and is not stored.  tri_invert (tri.hpp) leaves both results packed
+// in one LDS tile; they are written out with coalesced stores,
 // together with the zeros of L^{-1} above the sub-block and of U^{-1} left of
 // it.  The off-diagonal 64x64 blocks of the inverses come from the GEMM rounds
 // of the recursive doubling (X21 = -B^{-1} C A^{-1} for L,
@@ -47,71 +37,6 @@ namespace selinv {
 // NB = 4 handles every 64-wide sub-block; NB = 1 and 2 (16- and 32-wide
 // blocks, far less LDS) serve the supernodes of at most 16 or 32 columns
 // whose normalisation runs in the same workgroup.
-template <int NB>
-struct TriSmem {
-    static constexpr int W = 16 * NB;
-    double Ds[W][65];        // Ds[c][r] = D(o + r, o + c), identity-padded; later a panel (64 rows)
-    double Xs[W][W + 1];     // Xs[c][r]: r > c: L^{-1}(r, c); r <= c: U^{-1}(r, c)
-    double Ts[4][16][17];    // per-wavefront 16x16 intermediate
-    double rd[W];            // 1 / U(c, c)
-};
-
-typedef double v4d_t __attribute__((ext_vector_type(4)));
-
-// L^{-1}(r, c) and U^{-1}(r, c) read from the packed tile (zero outside the
-// triangle; the unit diagonal of L^{-1} is implicit)
-template <class SM>
-__device__ __forceinline__ double linv_at(const SM &sm, int r, int c) {
-    return r > c ? sm.Xs[c][r] : (r == c ? 1.0 : 0.0);
-}
-template <class SM>
-__device__ __forceinline__ double uinv_at(const SM &sm, int r, int c) { return r <= c ? sm.Xs[c][r] : 0.0; }
-
-// One off-diagonal block at distance D, computed by the calling wavefront.
-// The lanes feed the MFMA with A(i = lane % 16, k = lane / 16) and
-// B(k = lane / 16, j = lane % 16); the result row is lane / 16 + 4 v, its
-// column lane % 16 (register v of the accumulator).
-template <int NB, int D>
-__device__ __forceinline__ void tri_offdiag(TriSmem<NB> &sm, int t, int lane, int wave) {
-    const bool upper = t >= NB - D;
-    const int i = upper ? t - (NB - D) : t + D;  // row block of the result
-    const int j = upper ? i + D : t;             // column block
-    const int kb = upper ? 16 * (i + 1) : 16 * j;  // contraction range [kb, kb + 16 D)
-    const int li = lane & 15, lk = lane >> 4;
-    v4d_t acc = {0, 0, 0, 0};
-#pragma unroll
-    for (int kk = 0; kk < 16 * D; kk += 4) {
-        const int k = kb + kk + lk;
-        // factor entry L(16 i + li, k) or U(16 i + li, k): strictly off the diagonal
-        const double a = sm.Ds[k][16 * i + li];
-        const double bv = upper ? uinv_at(sm, k, 16 * j + li) : linv_at(sm, k, 16 * j + li);
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bv, acc, 0, 0, 0);
-    }
-#pragma unroll
-    for (int v = 0; v < 4; v++) sm.Ts[wave][lk + 4 * v][li] = acc[v];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    v4d_t out = {0, 0, 0, 0};
-#pragma unroll
-    for (int kk = 0; kk < 16; kk += 4) {
-        const int r = 16 * i + li, c = 16 * i + kk + lk;
-        const double a = upper ? uinv_at(sm, r, c) : linv_at(sm, r, c);
-        out = __builtin_amdgcn_mfma_f64_16x16x4f64(a, sm.Ts[wave][kk + lk][li], out, 0, 0, 0);
-    }
-#pragma unroll
-    for (int v = 0; v < 4; v++) sm.Xs[16 * j + li][16 * i + lk + 4 * v] = -out[v];
-    // the wavefront's next task overwrites Ts
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
-template <int NB, int D>
-__device__ __forceinline__ void tri_round(TriSmem<NB> &sm, int lane, int wave) {
-    __syncthreads();
-    for (int t = wave; t < 2 * (NB - D); t += 4) tri_offdiag<NB, D>(sm, t, lane, wave);
-}
-
 // Normalisation and diagonal initialisation of a supernode with s, c_L,
 // c_U <= 64, after its inverses are complete in sm.Xs (FP64 arithmetic on
 // v_mfma_f64_16x16x4, results in the storage precision).  Every product is
@@ -192,7 +117,7 @@ __device__ __forceinline__ void tri_fused_epilogue(TriSmem<NB> &sm, const TriIte
 template <int NB>
 __device__ __forceinline__ void tri_base_item(const TriItem &it, TriSmem<NB> &sm) {
     constexpr int W = 16 * NB;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int s = it.s, o = it.j0, b = min(W, s - o);
     {
         // all loads of a thread in flight at once; addresses clamped into
@@ -214,30 +139,7 @@ __device__ __forceinline__ void tri_base_item(const TriItem &it, TriSmem<NB> &sm
         }
     }
     __syncthreads();
-    if (wave < NB) {
-        const int base = 16 * wave, c = lane & 15;
-        const bool up = (lane & 16) != 0;  // lanes 32..63 repeat lanes 0..31 and store nothing
-        double x[16];
-#pragma unroll
-        for (int r = 0; r < 16; r++) x[r] = r == c ? 1.0 : 0.0;
-#pragma unroll
-        for (int k = 0; k < 16; k++) {
-            if (up) x[k] = x[k] * sm.rd[base + k];
-#pragma unroll
-            for (int r = k + 1; r < 16; r++)
-                x[r] = fma(-(up ? sm.Ds[base + r][base + k] : sm.Ds[base + k][base + r]), x[k], x[r]);
-        }
-        if (lane < 32) {
-#pragma unroll
-            for (int r = 0; r < 16; r++) {
-                if (!up && r > c) sm.Xs[base + c][base + r] = x[r];  // L^{-1}(r, c)
-                if (up && r >= c) sm.Xs[base + r][base + c] = x[r];  // U^{-1}(c, r)
-            }
-        }
-    }
-    if constexpr (NB >= 2) tri_round<NB, 1>(sm, lane, wave);
-    if constexpr (NB >= 3) tri_round<NB, 2>(sm, lane, wave);
-    if constexpr (NB >= 4) tri_round<NB, 3>(sm, lane, wave);
+    tri_invert<NB>(sm, lane, wave);
     __syncthreads();
     if (it.fused) {
         tri_fused_epilogue<NB>(sm, it, lane, wave);

@@ -7,9 +7,8 @@
 // The host orchestration (runtime.hip) runs the levels of the supernodal
 // dependency graph from the deepest up.  Per level, in 64-column steps j0 of
 // every supernode's diagonal block:
-//   lu_tile_kernel   LU of the 64 x 64 tile at (j0, j0), one wave;
-//   tri_base_kernel  the inverses of the tile's unit L and of its U
-//                    (kernels.hip);
+//   lu_tile_kernel   LU of the 64 x 64 tile at (j0, j0) and the inverses of
+//                    its unit L and of its U;
 //   grouped GEMM     the solves against the tile as products with those
 //                    inverses, in place: the rows of D below the tile and of
 //                    the L panel times U11^{-1}, L11^{-1} times the columns of
@@ -25,6 +24,7 @@
 #include "device_types.hpp"
 #include "kernels.hpp"
 #include "tiles.hpp"
+#include "tri.hpp"
 
 namespace selinv {
 
@@ -50,48 +50,139 @@ __global__ __launch_bounds__(256) void scatter_values_kernel(const int64_t *__re
     gptr_w(dst)[off] = v;
 }
 
-// Right-looking elimination of the b x b tile (b = min(64, s - j0)) at
-// (j0, j0) of the column-major s x s block D, one wave per tile: lane i holds
-// row i of the tile in registers.  At step k lane k publishes its row (the
-// pivot row U(k, k:)) in LDS; every lane below it scales its entry of column
-// k by the pivot's reciprocal and takes the rank-one update of the rest of its
-// row.  A zero or non-finite pivot lowers *bad to its permuted column
-// f + j0 + k (the arithmetic goes on; the host reports the failure).
-__global__ __launch_bounds__(64) void lu_tile_kernel(const LuTile *__restrict__ items, int32_t *bad) {
-    __shared__ double urow[2][64];  // pivot rows of even / odd steps
+// LU of the 16 nb wide block in sm.Ds (identity-padded) by one workgroup, in
+// 16-column panels: one wavefront eliminates the panel with lane i holding row
+// i of it in registers (the pivot row reaches the other lanes through scalar
+// registers, v_readlane), the other three form the rows of U right of it, 16
+// columns each (lane = column, substitution with the panel's unit L), then all
+// four update the rest on v_mfma_f64_16x16x4.
+__device__ __forceinline__ double lane_value(double v, int lane) {
+    const int64_t b = __builtin_bit_cast(int64_t, v);
+    const uint32_t lo = __builtin_amdgcn_readlane((int)b, lane);
+    const uint32_t hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __builtin_bit_cast(double, (int64_t)(((uint64_t)hi << 32) | lo));
+}
+
+template <class SM>
+__device__ __forceinline__ void lu_factor_block(SM &sm, int nb, int lane, int wave) {
+    const int li = lane & 15, lk = lane >> 4;
+    for (int kb = 0; kb < nb; kb++) {
+        const int k0 = 16 * kb;
+        if (wave == 0) {
+            double a[16];
+#pragma unroll
+            for (int c = 0; c < 16; c++) a[c] = sm.Ds[k0 + c][lane];
+            // the reciprocal of the next pivot is formed as soon as its column is
+            // updated, beside the updates of the other columns
+            double rp = 1.0 / lane_value(a[0], k0);
+#pragma unroll
+            for (int k = 0; k < 15; k++) {
+                double u[16];
+#pragma unroll
+                for (int c = k + 1; c < 16; c++) u[c] = lane_value(a[c], k0 + k);
+                // rows above keep their values (l = 0); a non-finite u could
+                // spoil them, but then the pivot of its column is rejected too
+                const bool below = lane > k0 + k;
+                const double l = below ? a[k] * rp : 0.0;
+                a[k] = below ? l : a[k];
+                a[k + 1] = fma(-l, u[k + 1], a[k + 1]);
+                rp = 1.0 / lane_value(a[k + 1], k0 + k + 1);
+#pragma unroll
+                for (int c = k + 2; c < 16; c++) a[c] = fma(-l, u[c], a[c]);
+            }
+            if (lane > k0 + 15) a[15] *= rp;
+#pragma unroll
+            for (int c = 0; c < 16; c++) sm.Ds[k0 + c][lane] = a[c];
+        }
+        __syncthreads();
+        if (kb + 1 == nb) break;
+        if (wave > 0 && lane < 16 && kb + wave < nb) {  // block column kb + wave
+            double m[16], x[16];  // row `lane` of the panel's unit L, column `lane` of the block
+            double *col = sm.Ds[k0 + 16 * wave + lane];
+#pragma unroll
+            for (int r = 0; r < 16; r++) {
+                m[r] = sm.Ds[k0 + r][k0 + lane];
+                x[r] = col[k0 + r];
+            }
+            tri_substitute<0, false>(m, x, 1.0);
+#pragma unroll
+            for (int r = 1; r < 16; r++) col[k0 + r] = x[r];
+        }
+        __syncthreads();
+        const int nt = nb - kb - 1;
+        for (int t = wave; t < nt * nt; t += 4) {
+            const int i = k0 + 16 + 16 * (t % nt), j = k0 + 16 + 16 * (t / nt);
+            v4d_t acc;
+#pragma unroll
+            for (int v = 0; v < 4; v++) acc[v] = sm.Ds[j + li][i + lk + 4 * v];
+#pragma unroll
+            for (int kk = 0; kk < 16; kk += 4)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-sm.Ds[k0 + kk + lk][i + li], sm.Ds[j + li][k0 + kk + lk],
+                                                           acc, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; v++) sm.Ds[j + li][i + lk + 4 * v] = acc[v];
+        }
+        __syncthreads();
+    }
+}
+
+// The b x b tile (b = min(64, s - j0)) at (j0, j0) of the column-major s x s
+// block D: its LU in place, and the inverses of its unit L and of its U into
+// the same place of Linv and Uinv (the solves of the rows below it and of the
+// columns right of it are products with them).  A zero or non-finite pivot
+// lowers *bad to its permuted column f + j0 + k (the arithmetic goes on; the
+// host reports the failure).
+// Bound by the chain of 64 pivots, each a reciprocal and a rank-one update.
+// One wavefront over the whole tile (64-wide rows in registers, the pivot row
+// through LDS) took 36 us a launch and the inverses another 15 us in a launch
+// of their own (2D 256^2); blocked by 16, both take 22 us in one launch (about
+// 9 of them the pivot chain, 3.5 the rows of U, 5.5 the inverses).
+__global__ __launch_bounds__(256) void lu_tile_kernel(const LuTile *__restrict__ items, int32_t *bad) {
+    __shared__ TriSmem<4> sm;
     const LuTile it = items[blockIdx.x];
-    const int i = threadIdx.x;
-    const int s = it.s, j0 = it.j0, b = min(64, s - j0);
-    SELINV_GLOBAL double *D = gptr_w(it.D) + j0 + (int64_t)j0 * s;
-    double a[64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int s = it.s, b = min(64, s - it.j0), nb = (b + 15) / 16;
+    const int64_t at = it.j0 + (int64_t)it.j0 * s;
+    SELINV_GLOBAL double *D = gptr_w(it.D) + at;
+    {
+        // all loads in flight at once (clamped addresses), identity padding
+        double v[16];
 #pragma unroll
-    for (int c = 0; c < 64; c++) a[c] = (i < b && c < b) ? D[i + (int64_t)c * s] : (i == c ? 1.0 : 0.0);
+        for (int q = 0; q < 16; q++) v[q] = D[min(lane, b - 1) + (int64_t)min(wave + 4 * q, b - 1) * s];
 #pragma unroll
-    for (int k = 0; k < 64; k++) {
-        if (k < b) {
-            double *u = urow[k & 1];
-            if (i == k) {
-#pragma unroll
-                for (int c = k; c < 64; c++) u[c] = a[c];
-            }
-            __syncthreads();
-            const double p = u[k];
-            if (i == 0 && !(p != 0.0 && isfinite(p))) atomicMin(bad, it.f + j0 + k);
-            if (i > k) {
-                double ur[64];  // the pivot row, all reads in flight before the update
-#pragma unroll
-                for (int c = k + 1; c < 64; c++) ur[c] = u[c];
-                const double l = a[k] * (1.0 / p);
-                a[k] = l;
-#pragma unroll
-                for (int c = k + 1; c < 64; c++) a[c] = fma(-l, ur[c], a[c]);
-            }
+        for (int q = 0; q < 16; q++) {
+            const int c = wave + 4 * q;
+            sm.Ds[c][lane] = (lane < b && c < b) ? v[q] : (lane == c ? 1.0 : 0.0);
         }
     }
-    if (i < b) {
+    __syncthreads();
+    lu_factor_block(sm, nb, lane, wave);
+    if (tid < 64) {
+        const double p = sm.Ds[tid][tid];
+        sm.rd[tid] = 1.0 / p;
+        if (tid < b && !(p != 0.0 && isfinite(p))) atomicMin(bad, it.f + it.j0 + tid);
+    }
 #pragma unroll
-        for (int c = 0; c < 64; c++)
-            if (c < b) D[i + (int64_t)c * s] = a[c];
+    for (int q = 0; q < 16; q++) {
+        const int c = wave + 4 * q;
+        if (lane < b && c < b) D[lane + (int64_t)c * s] = sm.Ds[c][lane];
+    }
+    __syncthreads();
+    if (nb > 2)
+        tri_invert<4>(sm, lane, wave);
+    else if (nb == 2)
+        tri_invert<2>(sm, lane, wave);
+    else
+        tri_invert<1>(sm, lane, wave);
+    __syncthreads();
+    SELINV_GLOBAL double *Linv = gptr_w(it.Linv) + at, *Uinv = gptr_w(it.Uinv) + at;
+#pragma unroll
+    for (int q = 0; q < 16; q++) {
+        const int c = wave + 4 * q;
+        if (lane < b && c < b) {
+            Linv[lane + (int64_t)c * s] = linv_at(sm, lane, c);
+            Uinv[lane + (int64_t)c * s] = uinv_at(sm, lane, c);
+        }
     }
 }
 
@@ -213,7 +304,7 @@ hipError_t launch_scatter_values(const int64_t *loc, const double *vals, const i
 
 hipError_t launch_lu_tiles(const LuTile *items, int count, int32_t *bad, hipStream_t st) {
     if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(lu_tile_kernel, dim3(count), dim3(64), 0, st, items, bad);
+    hipLaunchKernelGGL(lu_tile_kernel, dim3(count), dim3(256), 0, st, items, bad);
     return hipGetLastError();
 }
 

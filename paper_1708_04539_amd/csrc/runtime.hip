@@ -226,11 +226,11 @@ struct Runner {
 
 // Work lists of the device LU (selinv_factor_device), built once per handle:
 // per level (deepest first) and per 64-column step of the diagonal blocks one
-// launch each of tile LUs, tile inverses, solves (products with the
+// launch each of tile LUs with their inverses, solves (products with the
 // inverses) and trailing updates, then the Schur complement products W_K and
 // their scatter into the ancestors.
 struct LuPlan {
-    enum : int { L_TILES = 0, L_TRI = 1, L_SOLVE = 2, L_UPDATE = 3, L_SCHUR = 4, L_SCATTER = 5 };
+    enum : int { L_TILES = 0, L_SOLVE = 1, L_UPDATE = 2, L_SCHUR = 3, L_SCATTER = 4 };
     struct Launch {
         int kind;
         int64_t first;
@@ -238,7 +238,6 @@ struct LuPlan {
     };
     std::vector<Launch> launches;
     LuTile *d_lu = nullptr;
-    TriItem *d_tri = nullptr;
     GemmProb *d_probs = nullptr;
     GemmTile *d_tiles = nullptr;
     GatherTile *d_sc = nullptr;
@@ -248,7 +247,7 @@ struct LuPlan {
     int64_t *d_emb = nullptr;  // complex handles: source of every entry of the real form
     DevAlloc al;
     ~LuPlan() {
-        for (void *q : {(void *)d_lu, (void *)d_tri, (void *)d_probs, (void *)d_tiles, (void *)d_sc, (void *)d_mat,
+        for (void *q : {(void *)d_lu, (void *)d_probs, (void *)d_tiles, (void *)d_sc, (void *)d_mat,
                         (void *)d_W, (void *)d_bad, (void *)d_emb})
             al.put(q);
     }
@@ -1887,7 +1886,6 @@ static selinv_status build_lu(selinv_handle h) {
     auto L = std::make_unique<LuPlan>();
     L->al = h->al;
     std::vector<LuTile> lus;
-    std::vector<TriItem> tris;
     std::vector<GemmProb> probs;
     std::vector<GemmTile> tiles;
     std::vector<GatherTile> scs;
@@ -1937,7 +1935,7 @@ static selinv_status build_lu(selinv_handle h) {
         for (int32_t K : Ks) smax = std::max(smax, h->sn[K].s);
         for (int j0 = 0; j0 < smax; j0 += 64) {
             // solves first (launch L_SOLVE), trailing updates after them
-            const size_t l0 = lus.size(), t0 = tris.size(), g0 = tiles.size();
+            const size_t l0 = lus.size(), g0 = tiles.size();
             struct Upd {
                 const double *A;
                 int64_t lda;
@@ -1962,14 +1960,7 @@ static selinv_status build_lu(selinv_handle h) {
                 // the L and U panels are row-contiguous operands: at most one
                 // leading dimension inside a load
                 if (std::max(cl, cu) >= 1 << 29) ok = false;
-                lus.push_back(LuTile{D, s, j0, r.f, 0});
-                TriItem ti{};
-                ti.D = D;
-                ti.Linv = Li0 + r.off_d;
-                ti.Uinv = Ui0 + r.off_d;
-                ti.s = s;
-                ti.j0 = j0;
-                tris.push_back(ti);
+                lus.push_back(LuTile{D, Li0 + r.off_d, Ui0 + r.off_d, s, j0, r.f, 0});
                 const double *Lt = Li0 + r.off_d + tile, *Ut = Ui0 + r.off_d + tile;
                 // solves, in place: every product has one 64-wide tile along
                 // the solved dimension, so each workgroup reads only the rows
@@ -2005,7 +1996,6 @@ static selinv_status build_lu(selinv_handle h) {
                 }
             }
             mark(LuPlan::L_TILES, l0, lus.size());
-            mark(LuPlan::L_TRI, t0, tris.size());
             mark(LuPlan::L_SOLVE, g0, tiles.size());
             const size_t g1 = tiles.size();
             for (const Upd &u : upd) gemm(u.A, u.lda, u.opA, u.B, u.ldb, u.opB, u.C, u.ldc, u.M, u.N, u.K, -1.0, 1.0);
@@ -2051,7 +2041,6 @@ static selinv_status build_lu(selinv_handle h) {
         return SELINV_E_STATE;
     }
     HIPCHK(h->err, upload(L->al, &L->d_lu, lus), "upload LU tiles");
-    HIPCHK(h->err, upload(L->al, &L->d_tri, tris), "upload tile inverses");
     HIPCHK(h->err, upload(L->al, &L->d_probs, probs), "upload LU products");
     HIPCHK(h->err, upload(L->al, &L->d_tiles, tiles), "upload LU product tiles");
     HIPCHK(h->err, upload(L->al, &L->d_sc, scs), "upload scatter tiles");
@@ -2119,7 +2108,6 @@ selinv_status selinv_factor_device(selinv_handle h, const double *values, void *
         hipError_t e = hipSuccess;
         switch (l.kind) {
             case LuPlan::L_TILES: e = launch_lu_tiles(L.d_lu + l.first, l.count, L.d_bad, s); break;
-            case LuPlan::L_TRI: e = launch_tri_base(L.d_tri + l.first, l.count, 4, s); break;
             case LuPlan::L_SOLVE:
                 e = launch_gemm(GEMM_PRO_F64, CMP_F64, GEMM_TILE_64, L.d_probs, L.d_tiles + l.first, l.count, s);
                 break;

@@ -72,3 +72,42 @@ def test_tile_widths_agree(sizes, prec):
                 assert np.array_equal(x, got[c])
             s.close()
     assert cap in got
+
+
+# diagonal tiles of the device LU: one 64-wide block in 16-column panels, its
+# last panel ragged, and a second block
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 32, 33, 48, 63, 64, 65, 81, 129])
+def test_device_lu_tile_edges(n):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_1708_04539_amd import selinv as si
+    print("[case] device LU, one dense block of", n, flush=True)
+    cp, ri, v, _ = random_sparse(n, 1.0, n)
+    s = si.SelInv(n, cp, ri, None, n, n, 0)
+    assert s.info["max_s"] == n
+    s.factor_device(torch.from_numpy(v).cuda())
+    s.run("fp64")
+    r, c, x = s.export()
+    o = Oracle(n, cp, ri, None, n, n, 0, 0).factor(v).selinv()
+    r2, c2, ref = o.export()
+    assert np.array_equal(r, r2) and np.array_equal(c, c2)
+    assert np.abs(x - ref).max() / np.abs(ref).max() <= TOL["fp64"]
+
+
+@pytest.mark.parametrize("k", [0, 15, 16, 40, 63, 64, 79])
+def test_device_lu_names_the_first_zero_pivot(k):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_1708_04539_amd import selinv as si
+    print("[case] device LU, zero pivot at", k, flush=True)
+    n = 80
+    a = np.full((n, n), 0.25) + np.diag(np.full(n, float(n)))
+    a[k, :] = 0.0  # an exactly zero row of the block: its pivot is zero whatever precedes it
+    cp = np.arange(0, n * n + 1, n, dtype=np.int64)
+    ri = np.tile(np.arange(n, dtype=np.int32), n)
+    s = si.SelInv(n, cp, ri, None, n, n, 0)
+    with pytest.raises(si.SelinvError) as e:
+        s.factor_device(torch.from_numpy(a.T.ravel().copy()).cuda())
+    assert e.value.status == "ZERO_PIVOT" and f"permuted column {k} " in str(e.value)
