@@ -224,8 +224,8 @@ selinv_status selinv_run(selinv_handle h, selinv_precision prec, void *stream);
 selinv_status selinv_run_graph(selinv_handle h, selinv_precision prec, void *stream);
 
 /* How the level sweep is launched.
- *   0 (auto, default): persistent when the levels are too small to fill the
- *     device on their own, per-level launches otherwise;
+ *   0 (auto, default): as 1, unless a tuning of the handle chose the
+ *     persistent form;
  *   1: one launch per kernel class per level (gather, steps 3+5, step 4);
  *   2: one persistent, dependency-driven launch for the whole sweep
  *     (section on inter-supernode parallelism: tasks start as soon as their

@@ -371,6 +371,16 @@ constexpr double kTile32Below = 512;
 // levels at least this wide (in supernodes) start the part of the prologue
 // that runs beside the sweep of the levels above
 constexpr int kSplitWidth = 64;
+// The fork of that part costs 15-30 us (two queues, their joins, and the upper
+// levels' launches waiting for compute units) and hides its time behind the
+// levels above: without a tuning it is made only if there are at least
+// kForkLevels of them and kForkItems 64-wide inversion workgroups to hide.
+// Measured, us a run, forked against not: 2D 256^2 376 / 430 (7 levels above,
+// 1203 workgroups), 3 grids of side 77-88 195 / 218 (5, 346); 45x165 203 / 179
+// (6, none), 59x195 237 / 211 (6, 192), 12 grids of side 64-256 1129 / 1092 (3,
+// 5683), 4 grids 562 / 558 (4, 2441).
+constexpr int kForkLevels = 5;
+constexpr int64_t kForkItems = 256;
 // split-K of step 4: levels whose step-4 launch has fewer 64x64 tiles than
 // this cut the k range of their products (k >= 2 kSplitKMin) into parts of at
 // least kSplitKMin, up to 8, aiming at about 1024 tiles
@@ -541,20 +551,6 @@ int add_prob(std::vector<GemmProb> &probs, const void *A, int opA, int lda,
     return 1;
 }
 
-// The persistent sweep pays off when the levels are too small to fill the
-// device on their own (launch latency dominates): use it when the average
-// level carries less than about two waves of 64x64 product tiles.
-bool persist_auto(const std::vector<selinv_handle> &hs) {
-    double tiles = 0;
-    int depth = 0;
-    for (auto h : hs) {
-        depth = std::max(depth, h->P.nlevels);
-        for (const SnRec &r : h->sn)
-            tiles += std::ceil(r.s / 64.0) * (std::ceil(r.cl / 64.0) + 2 * std::ceil(r.cu / 64.0));
-    }
-    return depth > 0 && tiles / depth < 512;
-}
-
 GatherTile gather_tile_of(selinv_handle h, int32_t mi, int32_t K, int a0, int b0, int32_t skip);
 selinv_status ensure_codes_all(selinv_handle h);
 
@@ -575,7 +571,7 @@ selinv_status build_sweep(std::vector<selinv_handle> &hs, const DevAlloc &al, in
     // the gather form asks for (2 every level, 1 none, 0 the tuning's
     // choice), in a level sweep only (the persistent sweep gathers), and
     // never a level of the fused small-supernode launch (decided below).
-    bool vg_ok = sweep_mode == SWEEP_LEVELS || (sweep_mode == SWEEP_AUTO && !persist_auto(hs));
+    bool vg_ok = sweep_mode != SWEEP_PERSISTENT;
     auto vg_wanted = [&](int d) {
         return gather_form == 2 || (gather_form == 0 && tn && d < (int)tn->vg.size() && tn->vg[d]);
     };
@@ -680,6 +676,17 @@ selinv_status build_sweep(std::vector<selinv_handle> &hs, const DevAlloc &al, in
                 S->split = d;
                 break;
             }
+        if (!tn && S->split > 0) {
+            // 64-wide inversion workgroups of the part that would be forked
+            int64_t side = 0;
+            for (auto h : hs)
+                for (int d = S->split; d < h->P.nlevels; d++)
+                    for (int32_t K : h->P.levels[d]) {
+                        const SnRec &r = h->sn[K];
+                        if (!fused_prologue(r) || r.s > 32) side += (r.s + 63) / 64;
+                    }
+            if (S->split < kForkLevels || side < kForkItems) S->split = 0;
+        }
         if (tn && tn->no_fork == 1) S->split = 0;
         if (tn) S->side_chunk = tn->side_chunk;
         // part of each level
@@ -1158,9 +1165,13 @@ selinv_status build_sweep(std::vector<selinv_handle> &hs, const DevAlloc &al, in
         else
             S->lev_bytes_gather[d] += src;
     }
-    // persistent task queue: level by level from the root; per level all
-    // gather tiles, then the step-3 tiles, the step-5 tiles, the step-4 tiles
-    {
+    // persistent task queue (on request only: level launches are faster at
+    // every size, 83 us against 125 us on the 2D 32^2 grid and 375 us against
+    // 930 us on 256^2, as the queue pays agent-scope release and acquire per
+    // task): level by level from the root; per level all gather tiles, then the
+    // step-3 tiles, the step-5 tiles, the step-4 tiles
+    S->persistent = sweep_mode == SWEEP_PERSISTENT;
+    if (S->persistent) {
         std::vector<PTask> pt;
         std::vector<PSn> psn(nsn);
         std::vector<int32_t> deps;
@@ -1242,25 +1253,21 @@ selinv_status build_sweep(std::vector<selinv_handle> &hs, const DevAlloc &al, in
             if (k.type == PT_STEP35 && last_gather[k.gid] > t) X.violations++;
             if (k.type == PT_STEP4 && last_zu[k.gid] > t) X.violations++;
         }
-        const bool small = pt.size() <= 400000;
-        S->persistent = sweep_mode == SWEEP_PERSISTENT || (sweep_mode == SWEEP_AUTO && small && persist_auto(hs));
-        if (S->persistent) {
-            if (pt.size() >= (size_t)INT32_MAX) {
-                err = "persistent task queue too long";
-                return SELINV_E_INVALID_ARG;
-            }
-            S->ntasks = (int32_t)pt.size();
-            S->ncnt = 3 * (int64_t)nsn;
-            std::vector<int32_t> zero(S->ncnt + 2, 0);
-            HIPCHK(err, upload(S->al, &S->d_ptasks, pt), "upload tasks");
-            HIPCHK(err, upload(S->al, &S->d_psn, psn), "upload task deps");
-            HIPCHK(err, upload(S->al, &S->d_deps, deps), "upload task deps");
-            HIPCHK(err, upload(S->al, &S->d_cnt, zero), "upload counters");
-            S->grid = persist_grid(mode_of(prec));
-            if (S->grid <= 0) {
-                err = "could not size the persistent grid";
-                return SELINV_E_DEVICE;
-            }
+        if (pt.size() >= (size_t)INT32_MAX) {
+            err = "persistent task queue too long";
+            return SELINV_E_INVALID_ARG;
+        }
+        S->ntasks = (int32_t)pt.size();
+        S->ncnt = 3 * (int64_t)nsn;
+        std::vector<int32_t> zero(S->ncnt + 2, 0);
+        HIPCHK(err, upload(S->al, &S->d_ptasks, pt), "upload tasks");
+        HIPCHK(err, upload(S->al, &S->d_psn, psn), "upload task deps");
+        HIPCHK(err, upload(S->al, &S->d_deps, deps), "upload task deps");
+        HIPCHK(err, upload(S->al, &S->d_cnt, zero), "upload counters");
+        S->grid = persist_grid(mode_of(prec));
+        if (S->grid <= 0) {
+            err = "could not size the persistent grid";
+            return SELINV_E_DEVICE;
         }
     }
     // gather tiles stay inside their supernode's G block

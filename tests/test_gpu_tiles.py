@@ -111,3 +111,33 @@ def test_device_lu_names_the_first_zero_pivot(k):
     with pytest.raises(si.SelinvError) as e:
         s.factor_device(torch.from_numpy(a.T.ravel().copy()).cuda())
     assert e.value.status == "ZERO_PIVOT" and f"permuted column {k} " in str(e.value)
+
+
+# the level sweep's own choices (no tuning): level launches at every size, the
+# prologue of the lower levels forked or not; neither changes a result
+@pytest.mark.parametrize("dims,cap", [((5, 4), 8), ((45, 165), 139), ((77, 81), 128), ((160, 150), 96)],
+                         ids=["5x4", "45x165", "77x81", "160x150"])
+@pytest.mark.parametrize("prec", ["fp64", "mixed_fp32"])
+def test_policy_sweep_equals_plain_levels(dims, cap, prec):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_1708_04539_amd import selinv as si
+    from workloads import config_grid
+    print("[case] sweep policy", dims, prec, flush=True)
+    w = config_grid("p", dims, "box", "sym_perturbed", 0.1, 0, cap, 64, delta=0.15)
+    s = si.SelInv(w.n, w.colptr, w.rowind, w.perm, w.max_super, w.relax, w.pad_pct).factor(w.values)
+    st = torch.cuda.Stream()
+    s.run(prec, stream=st)
+    assert s.sweep_is_persistent(prec) == 0
+    _, _, x = s.export(sort=False)
+    for _ in range(3):
+        s.run(prec, stream=st, graph=True)
+        _, _, g = s.export(sort=False)
+        assert np.array_equal(x, g)
+    L = s.info["nlevels"]
+    for fork in (0, 1):  # side stream from the first wide level on, none
+        s.set_tuning([4, L, 1, 0, 0, 0, fork, 0] + [0, 0, 0, 0] * L, prec)
+        s.run(prec, stream=st)
+        _, _, y = s.export(sort=False)
+        assert np.array_equal(x, y)
