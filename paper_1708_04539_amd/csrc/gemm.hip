@@ -31,20 +31,6 @@
 
 namespace selinv {
 
-// ROLE only names the launch site in profiles (0: triangular inversion,
-// normalisation and diagonal initialisation; 1: products of steps 3 and 5;
-// 2: product of step 4); the code is the same.
-// Workgroups are dispatched to the 8 XCDs round robin (workgroup b to XCD
-// b mod 8), and each XCD has its own L2.  The tile list is ordered row-block
-// major, so tiles that share a strip of op(A) are neighbours; the remap gives
-// each XCD one contiguous range of the list, so that such tiles run on the
-// same XCD at about the same time and share the strip in its L2.
-__device__ __forceinline__ int xcd_tile(int b, int n) {
-    constexpr int X = 8;
-    const int q = n / X, r = n % X, x = b % X, i = b / X;
-    return x * q + min(x, r) + i;
-}
-
 // LDS stages of the tiles that load straight into LDS
 template <int MODE, int BM>
 struct DmaStages {
@@ -57,6 +43,9 @@ struct DmaStages {
 template <int MODE, int BM, typename TA>
 constexpr bool kDmaTile = (BM == 64 || (BM == 128 && MODE == CMP_F32)) && MODE != CMP_BF16X3 && std::is_same<TA, typename Mode<MODE>::T>::value;
 
+// ROLE only names the launch site in profiles (0: triangular inversion,
+// normalisation and diagonal initialisation; 1: products of steps 3 and 5;
+// 2: product of step 4); the code is the same.
 // Occupancy: at least four workgroups per compute unit for the 32- and
 // 64-wide tiles (at most 128 VGPRs), two for the 128-wide ones.
 template <int MODE, int BM, int BN, typename TA, typename TC, int ROLE>

@@ -15,11 +15,11 @@
 //                    D right of the tile, the rows of the U panel times
 //                    L11^{-T};
 //   grouped GEMM     the trailing updates of the block and the panels;
-// then the Schur complement product W_K = -L(R_L, K) U(K, R_U) (grouped GEMM)
-// and scatter_update_kernel, which adds W_K to the blocks of the ancestors.
+// then schur_scatter_kernel, which forms the Schur complement product W_K =
+// -L(R_L, K) U(K, R_U) and adds it to the blocks of the ancestors.
 #include <hip/hip_runtime.h>
 
-#include <climits>
+#include <algorithm>
 
 #include "device_types.hpp"
 #include "kernels.hpp"
@@ -186,25 +186,33 @@ __global__ __launch_bounds__(256) void lu_tile_kernel(const LuTile *__restrict__
     }
 }
 
-// One 64 x 64 tile of W_K (c_L x c_U column-major at W + g_off) per
-// workgroup.  W_K(a, b) belongs to entry (R_L(K)[a], R_U(K)[b]) of At, which
-// lies in the diagonal block of J (I = J), the L panel of J (I > J) or the U
-// panel of I (I < J), I and J the supernodes of its row and column; the
-// relative-index maps give its place there.  As in the gather of the
-// selected inversion (the same positions, read there), the tile's row and
-// column records go to LDS first; the tile itself is staged in LDS, then the
-// diagonal and L-side entries are added with the threads along the rows
+// One 64 x 64 tile of W_K = -L(R_L,K) U(K,R_U) (c_L x c_U) per workgroup, added
+// to the blocks of the ancestors.  W_K(a, b) belongs to entry (R_L(K)[a],
+// R_U(K)[b]) of At, which lies in the diagonal block of J (I = J), the L panel
+// of J (I > J) or the U panel of I (I < J), I and J the supernodes of its row
+// and column; the relative-index maps give its place there.  As in the gather
+// of the selected inversion (the same positions, read there), the tile's row
+// and column records go to LDS first; the product tile follows into LDS, then
+// the diagonal and L-side entries are added with the threads along the rows
 // (contiguous in the L panels) and the U-side entries along the columns
 // (contiguous in the U panels).  Supernodes of one level update the same
 // entries of their common ancestors, hence the atomic adds.
-__global__ __launch_bounds__(256) void scatter_update_kernel(const MatDev *__restrict__ mat,
-                                                             const GatherTile *__restrict__ tiles,
-                                                             const double *__restrict__ W, double *diag,
-                                                             double *lpan, double *upan) {
-    __shared__ double tileS[64][65];  // [b][a]
+// Bound by the atomic adds and their scattered places.  W_K in memory between
+// a product launch and a scatter launch (16 bytes an entry and a launch more a
+// level) took 2.19 ms on the 3D 40^3 27-point matrix and 275 us on the 2D 256^2
+// one; in one launch 1.82 ms and 187 us.
+__global__ __launch_bounds__(256) void schur_scatter_kernel(const MatDev *__restrict__ mat,
+                                                            const GatherTile *__restrict__ tiles, double *diag,
+                                                            double *lpan, double *upan) {
+    union Shared {
+        DmaSmem<64, 64, 2> g;
+        double t[64][65];  // [b][a]
+    };
+    __shared__ Shared sm;
+    double(&tileS)[64][65] = sm.t;
     __shared__ int32_t rowR[64], rowI[64], colJ[64];
     __shared__ int64_t rowUp[64], rowUoff[64], colDiag[64], colLow[64], colLoff[64];
-    const GatherTile gt = tiles[blockIdx.x];
+    const GatherTile gt = tiles[xcd_tile(blockIdx.x, gridDim.x)];
     const MatDev &M = *mat;
     const SELINV_GLOBAL SnRec *sn = gptr(M.sn);
     const SELINV_GLOBAL int32_t *supof = gptr(M.supof);
@@ -237,12 +245,27 @@ __global__ __launch_bounds__(256) void scatter_update_kernel(const MatDev *__res
             colLoff[t] = lo + a0;
         }
     }
-    const SELINV_GLOBAL double *Wk = gptr(W) + gt.g_off;
     constexpr int PER = 64 * 64 / 256;
+    {
+        GemmProb p;
+        p.A = lpan + sn[K].off_l;
+        p.B = upan + sn[K].off_u;
+        p.M = p.lda = cl;
+        p.N = p.ldb = cu;
+        p.K = sn[K].s;
+        p.ktri = p.cpx = 0;
+        AccTile<CMP_F64, 64, 64> w;
+        DmaProduct<CMP_F64, 64, 64, 2, 0, 1>::form(p, a0, b0, sm.g, w);
+        __syncthreads();  // LDS free for the tile
+        const int lane = tid & 63, wave = tid >> 6;
 #pragma unroll
-    for (int t = 0; t < PER; t++) {
-        const int e = tid + 256 * t, ia = e & 63, ib = e >> 6;
-        if (ia < na && ib < nb) tileS[ib][ia] = Wk[(a0 + ia) + (int64_t)(b0 + ib) * cl];
+        for (int i = 0; i < 2; i++)
+#pragma unroll
+            for (int j = 0; j < 2; j++)
+#pragma unroll
+                for (int v = 0; v < 4; v++)
+                    tileS[(wave & 1) * 32 + j * 16 + (lane >> 4) + 4 * v][(wave >> 1) * 32 + i * 16 + (lane & 15)] =
+                        -w.a[i][j][v];
     }
     __syncthreads();
     const SELINV_GLOBAL int32_t *mapL = gptr(M.mapL);
@@ -294,6 +317,32 @@ __global__ __launch_bounds__(256) void scatter_update_kernel(const MatDev *__res
     }
 }
 
+// Zeros into the factor storage and the pivot flag to "none", in one launch
+// (three fills by hipMemsetAsync, of two kernels each, and one of the flag took
+// 34 us on the 2D 256^2 matrix (72 MB), this 12 us).
+__global__ __launch_bounds__(256) void clear_factors_kernel(double *diag, int64_t nd, double *lpan, int64_t nl,
+                                                            double *upan, int64_t nu, int32_t *bad) {
+    const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, n = gridDim.x * (int64_t)blockDim.x;
+    if (t == 0) *bad = LU_NO_BAD_PIVOT;
+    auto clear = [&](double *p, int64_t len) {
+        typedef double v2 __attribute__((ext_vector_type(2)));
+        SELINV_GLOBAL v2 *q = (SELINV_GLOBAL v2 *)p;  // every array starts 256-byte aligned
+        for (int64_t i = t; i < len / 2; i += n) q[i] = v2{0.0, 0.0};
+        if (t == 0 && (len & 1)) gptr_w(p)[len - 1] = 0.0;
+    };
+    clear(diag, nd);
+    clear(lpan, nl);
+    clear(upan, nu);
+}
+
+hipError_t launch_clear_factors(double *diag, int64_t nd, double *lpan, int64_t nl, double *upan, int64_t nu,
+                                int32_t *bad, hipStream_t st) {
+    const int64_t blocks = std::min<int64_t>(2048, (std::max(nd, std::max(nl, nu)) / 2 + 255) / 256 + 1);
+    hipLaunchKernelGGL(clear_factors_kernel, dim3((unsigned)blocks), dim3(256), 0, st, diag, nd, lpan, nl, upan, nu,
+                       bad);
+    return hipGetLastError();
+}
+
 hipError_t launch_scatter_values(const int64_t *loc, const double *vals, const int64_t *emb, int64_t nnz,
                                  double *diag, double *lpan, double *upan, hipStream_t st) {
     if (nnz <= 0) return hipSuccess;
@@ -308,10 +357,10 @@ hipError_t launch_lu_tiles(const LuTile *items, int count, int32_t *bad, hipStre
     return hipGetLastError();
 }
 
-hipError_t launch_scatter_update(const MatDev *mat, const GatherTile *tiles, int count, const double *W,
-                                 double *diag, double *lpan, double *upan, hipStream_t st) {
+hipError_t launch_schur_scatter(const MatDev *mat, const GatherTile *tiles, int count, double *diag, double *lpan,
+                                double *upan, hipStream_t st) {
     if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(scatter_update_kernel, dim3(count), dim3(256), 0, st, mat, tiles, W, diag, lpan, upan);
+    hipLaunchKernelGGL(schur_scatter_kernel, dim3(count), dim3(256), 0, st, mat, tiles, diag, lpan, upan);
     return hipGetLastError();
 }
 

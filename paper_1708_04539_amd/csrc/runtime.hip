@@ -227,10 +227,10 @@ struct Runner {
 // Work lists of the device LU (selinv_factor_device), built once per handle:
 // per level (deepest first) and per 64-column step of the diagonal blocks one
 // launch each of tile LUs with their inverses, solves (products with the
-// inverses) and trailing updates, then the Schur complement products W_K and
-// their scatter into the ancestors.
+// inverses) and trailing updates, then one launch of the Schur complement
+// products W_K and their scatter into the ancestors.
 struct LuPlan {
-    enum : int { L_TILES = 0, L_SOLVE = 1, L_UPDATE = 2, L_SCHUR = 3, L_SCATTER = 4 };
+    enum : int { L_TILES = 0, L_SOLVE = 1, L_UPDATE = 2, L_SCHUR = 3 };
     struct Launch {
         int kind;
         int64_t first;
@@ -242,13 +242,12 @@ struct LuPlan {
     GemmTile *d_tiles = nullptr;
     GatherTile *d_sc = nullptr;
     MatDev *d_mat = nullptr;
-    double *d_W = nullptr;  // W_K of one level
     int32_t *d_bad = nullptr;
     int64_t *d_emb = nullptr;  // complex handles: source of every entry of the real form
     DevAlloc al;
     ~LuPlan() {
         for (void *q : {(void *)d_lu, (void *)d_probs, (void *)d_tiles, (void *)d_sc, (void *)d_mat,
-                        (void *)d_W, (void *)d_bad, (void *)d_emb})
+                        (void *)d_bad, (void *)d_emb})
             al.put(q);
     }
 };
@@ -1901,15 +1900,7 @@ static selinv_status build_lu(selinv_handle h) {
     auto inside = [&](int64_t off, int64_t last, int64_t seg, int64_t len) {
         if (off < seg || last < 0 || off + last >= seg + len) ok = false;
     };
-    // W_K of one level, packed: the largest level decides the buffer
-    int64_t w_max = 0;
-    for (int32_t lev = 0; lev < P.nlevels; lev++) {
-        int64_t w = 0;
-        for (int32_t K : P.levels[lev]) w += (int64_t)h->sn[K].cl * h->sn[K].cu;
-        w_max = std::max(w_max, w);
-    }
-    HIPCHK(h->err, alloc_bytes(L->al, (void **)&L->d_W, w_max * 8), "alloc Schur complement buffer");
-    double *D0 = h->d_diag, *L0 = h->d_lpan, *U0 = h->d_upan, *W0 = L->d_W;
+    double *D0 = h->d_diag, *L0 = h->d_lpan, *U0 = h->d_upan;
     double *Li0 = h->d_Linv, *Ui0 = h->d_Uinv;  // the tile inverses (the run recomputes them)
     // C = alpha op(A) op(B) + beta C
     auto gemm = [&](const double *A, int64_t lda, int opA, const double *B, int64_t ldb, int opB, double *C,
@@ -2009,16 +2000,13 @@ static selinv_status build_lu(selinv_handle h) {
             mark(LuPlan::L_UPDATE, g1, tiles.size());
         }
         // W_K = -L(R_L, K) U(K, R_U) and its scatter into the ancestors
-        const size_t g0 = tiles.size(), c0 = scs.size();
-        int64_t w = 0;
+        const size_t c0 = scs.size();
         for (int32_t K : Ks) {
             const SnRec &r = h->sn[K];
-            const int s = r.s, cl = r.cl, cu = r.cu;
+            const int cl = r.cl, cu = r.cu;
             if (cl == 0 || cu == 0) continue;
-            inside(w, (int64_t)cl * cu - 1, 0, w_max);
-            gemm(L0 + r.off_l, cl, 0, U0 + r.off_u, cu, 1, W0 + w, cl, cl, cu, s, -1.0, 0.0);
             for (int a0 = 0; a0 < cl; a0 += 64)
-                for (int b0 = 0; b0 < cu; b0 += 64) scs.push_back(GatherTile{0, K, a0, b0, -1, cl, cu, 0, w, -1, 0, 0, 0, 0});
+                for (int b0 = 0; b0 < cu; b0 += 64) scs.push_back(GatherTile{0, K, a0, b0, -1, cl, cu, 0, 0, -1, 0, 0, 0, 0});
             // destinations of every entry of W_K
             const int32_t *RL = P.rl.data() + P.rl_ptr[K], *RU = P.ru.data() + P.ru_ptr[K];
             for (int b2 = 0; b2 < cu && ok; b2++) {
@@ -2038,10 +2026,8 @@ static selinv_status build_lu(selinv_handle h) {
                     }
                 }
             }
-            w += (int64_t)cl * cu;
         }
-        mark(LuPlan::L_SCHUR, g0, tiles.size());
-        mark(LuPlan::L_SCATTER, c0, scs.size());
+        mark(LuPlan::L_SCHUR, c0, scs.size());
     }
     if (!ok) {
         h->err = "device LU: work list outside the factor storage (inconsistent analysis)";
@@ -2105,10 +2091,8 @@ selinv_status selinv_factor_device(selinv_handle h, const double *values, void *
     LuPlan &L = *h->lu;
     hipStream_t s = (hipStream_t)stream;
     h->state = 0;  // the factor storage is rewritten from here on
-    HIPCHK(h->err, hipMemsetAsync(h->d_diag, 0, P.tot_d * 8, s), "clear diag");
-    HIPCHK(h->err, hipMemsetAsync(h->d_lpan, 0, P.tot_l * 8, s), "clear lpan");
-    HIPCHK(h->err, hipMemsetAsync(h->d_upan, 0, P.tot_u * 8, s), "clear upan");
-    HIPCHK(h->err, hipMemsetAsync(L.d_bad, 0x7f, sizeof(int32_t), s), "clear pivot flag");
+    HIPCHK(h->err, launch_clear_factors(h->d_diag, P.tot_d, h->d_lpan, P.tot_l, h->d_upan, P.tot_u, L.d_bad, s),
+           "clear factors");
     HIPCHK(h->err, launch_scatter_values(h->d_aloc, values, L.d_emb, P.nnz_a, h->d_diag, h->d_lpan, h->d_upan, s),
            "scatter values");
     for (const LuPlan::Launch &l : L.launches) {
@@ -2121,19 +2105,15 @@ selinv_status selinv_factor_device(selinv_handle h, const double *values, void *
             case LuPlan::L_UPDATE:
                 e = launch_gemm(GEMM_STEP4, CMP_F64, GEMM_TILE_64, L.d_probs, L.d_tiles + l.first, l.count, s);
                 break;
-            case LuPlan::L_SCHUR:
-                e = launch_gemm(GEMM_PRO_F64, CMP_F64, GEMM_TILE_64, L.d_probs, L.d_tiles + l.first, l.count, s);
-                break;
             default:
-                e = launch_scatter_update(L.d_mat, L.d_sc + l.first, l.count, L.d_W, h->d_diag, h->d_lpan,
-                                          h->d_upan, s);
+                e = launch_schur_scatter(L.d_mat, L.d_sc + l.first, l.count, h->d_diag, h->d_lpan, h->d_upan, s);
         }
         HIPCHK(h->err, e, "device LU launch");
     }
     int32_t bad = 0;
     HIPCHK(h->err, hipMemcpyAsync(&bad, L.d_bad, sizeof(bad), hipMemcpyDeviceToHost, s), "pivot flag");
     HIPCHK(h->err, hipStreamSynchronize(s), "device LU");
-    if (bad != 0x7f7f7f7f) {
+    if (bad != LU_NO_BAD_PIVOT) {
         h->err = "zero or non-finite pivot at permuted column " + std::to_string(bad) + " (original column " +
                  std::to_string(bad >= 0 && bad < (int32_t)P.p.size() ? P.p[bad] : -1) + ")";
         return SELINV_E_ZERO_PIVOT;

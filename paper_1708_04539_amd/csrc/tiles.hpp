@@ -26,6 +26,17 @@ __device__ __forceinline__ SELINV_GLOBAL T *gptr_w(T *p) {
     return (SELINV_GLOBAL T *)p;
 }
 
+// Workgroups are dispatched to the 8 XCDs round robin (workgroup b to XCD
+// b mod 8), and each XCD has its own L2.  The tile list is ordered row-block
+// major, so tiles that share a strip of op(A) are neighbours; the remap gives
+// each XCD one contiguous range of the list, so that such tiles run on the
+// same XCD at about the same time and share the strip in its L2.
+__device__ __forceinline__ int xcd_tile(int b, int n) {
+    constexpr int X = 8;
+    const int q = n / X, r = n % X, x = b % X, i = b / X;
+    return x * q + min(x, r) + i;
+}
+
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
@@ -803,114 +814,129 @@ __device__ __forceinline__ void dma_barrier() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
 
+// acc = op(A) op(B) of the BM x BN tile at (m0, n0), in the accumulators of
+// the workgroup's wavefronts (see gemm_store).
+template <int MODE, int BM, int BN>
+struct AccTile {
+    typename Mode<MODE>::Acc a[BM / 32][BN / 32];
+};
+template <int MODE, int BM, int BN, int ST, int OPA, int OPB>
+struct DmaProduct {
+    static __device__ __forceinline__ void form(const GemmProb &p, const int m0, const int n0,
+                                                DmaSmem<BM, BN, ST> &sm, AccTile<MODE, BM, BN> &t) {
+        typedef typename Mode<MODE>::T T;
+        typedef typename Mode<MODE>::Acc Acc;
+        auto &acc = t.a;
+        static_assert(MODE == CMP_F64 || MODE == CMP_F32, "operands in the arithmetic's own type");
+        static_assert(ST == 2 || ST == 3, "stages");
+        typedef DmaOperand<T, BM, OPA == 1> OA;
+        typedef DmaOperand<T, BN, OPB == 0> OB;
+        constexpr int BK = OA::BK, WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int wm = wave >> 1, wn = wave & 1, li = lane & 15, lk = lane >> 4;
+        const int K = p.K;
+        OA a;
+        OB b;
+        a.init(p.A, p.lda, m0, p.M, K, lane, wave);
+        b.init(p.B, p.ldb, n0, p.N, K, lane, wave);
+        lds_char *const lds = (lds_char *)&sm.b[0][0];
+        constexpr int SB = (BM + BN) * 128;  // bytes per stage
+        auto issue = [&](int c, int st) {
+            a.issue(lds + st * SB, c, wave);
+            b.issue(lds + st * SB + BM * 128, c, wave);
+        };
+#pragma unroll
+        for (int i = 0; i < TM; i++)
+#pragma unroll
+            for (int j = 0; j < TN; j++) acc[i][j] = Acc{0, 0, 0, 0};
+        // LDS offsets of this lane's operands (stage 0): of 16-row tile i at k
+        // step kk.  k-contiguous: the unit depends on kk, the tile is a constant
+        // further on; row-contiguous: the other way round.
+        constexpr int KS = BK / 4;
+        int oa[OPA == 1 ? KS : TM], ob[OPB == 0 ? KS : TN];
+#pragma unroll
+        for (int q = 0; q < (OPA == 1 ? KS : TM); q++)
+            oa[q] = OPA == 1 ? OA::at(wm * WM + li, 4 * q + lk) : OA::at(wm * WM + 16 * q + li, lk);
+#pragma unroll
+        for (int q = 0; q < (OPB == 0 ? KS : TN); q++)
+            ob[q] = BM * 128 + (OPB == 0 ? OB::at(wn * WN + li, 4 * q + lk) : OB::at(wn * WN + 16 * q + li, lk));
+        auto kstep = [&](int st, int q) {
+            T av[TM], bv[TN];
+#pragma unroll
+            for (int i = 0; i < TM; i++)
+                av[i] = *(const __attribute__((address_space(3))) T *)(lds + (OPA == 1 ? oa[q] : oa[i]) +
+                                                                       (st * SB + (OPA == 1 ? i * 16 * 128 : 4 * q * OA::RB)));
+#pragma unroll
+            for (int j = 0; j < TN; j++)
+                bv[j] = *(const __attribute__((address_space(3))) T *)(lds + (OPB == 0 ? ob[q] : ob[j]) +
+                                                                       (st * SB + (OPB == 0 ? j * 16 * 128 : 4 * q * OB::RB)));
+#pragma unroll
+            for (int i = 0; i < TM; i++)
+#pragma unroll
+                for (int j = 0; j < TN; j++) {
+                    if constexpr (MODE == CMP_F64)
+                        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(bv[j], av[i], acc[i][j], 0, 0, 0);
+                    else
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[j], av[i], acc[i][j], 0, 0, 0);
+                }
+        };
+        // chunks whose products are all zero by the operands' triangular
+        // structure are skipped, as in gemm_tile_op
+        const int klo = max((p.ktri & 1) ? (p.cpx ? 2 * n0 : n0) : 0, (p.ktri & 2) ? m0 : 0);
+        const int nch = (K + BK - 1) / BK, nfull = K / BK, c0 = min(klo / BK, nch);
+        constexpr int NI = OA::NI + OB::NI;  // loads per wavefront and chunk
+        if (c0 < nch) issue(c0, 0);
+        if constexpr (ST == 3) {
+            if (c0 + 1 < nch) issue(c0 + 1, 1);
+        }
+        // chunk c (stage S) has landed everywhere and chunk c - 1 is used up
+        auto arrive = [&](int c, int S) {
+            if (ST == 3 && c + 1 < nch)
+                dma_barrier<(ST == 3 ? NI : 0)>();
+            else
+                dma_barrier<0>();
+            if (c + ST - 1 < nch) issue(c + ST - 1, (S + ST - 1) % ST);
+        };
+        auto step = [&](int c, auto S_) {
+            constexpr int S = decltype(S_)::value;
+            arrive(c, S);
+#pragma unroll
+            for (int q = 0; q < KS; q++) kstep(S, q);
+        };
+        typedef std::integral_constant<int, 0> S0;
+        typedef std::integral_constant<int, 1> S1;
+        typedef std::integral_constant<int, ST - 1> SL;
+        for (int c = c0; c < nfull; c += ST) {
+            step(c, S0{});
+            if (c + 1 < nfull) step(c + 1, S1{});
+            if constexpr (ST == 3) {
+                if (c + 2 < nfull) step(c + 2, SL{});
+            }
+        }
+        if (max(c0, nfull) < nch) {
+            // last, partial chunk
+            const int S = max(nfull - c0, 0) % ST;
+            arrive(nch - 1, S);
+            const int kr = K - nfull * BK, nz = (4 - (kr & 3)) & 3;
+            for (int e = threadIdx.x; e < nz * (BM + BN); e += 256) {
+                const int k = kr + e / (BM + BN), r = e % (BM + BN);
+                const int o = r < BM ? OA::at(r, k) : BM * 128 + OB::at(r - BM, k);
+                *(__attribute__((address_space(3))) T *)(lds + S * SB + o) = (T)0;
+            }
+            dma_barrier<0>();
+#pragma unroll
+            for (int q = 0; q < KS; q++)
+                if (4 * q < kr) kstep(S, q);
+        }
+    }
+};
+
 template <int MODE, int BM, int BN, int ST, typename TC, bool CIN, int OPA, int OPB, bool PUSH, typename TG>
 __device__ __forceinline__ void gemm_tile_dma_op(const GemmProb &p, const int m0, const int n0,
                                                  DmaSmem<BM, BN, ST> &sm, const MatDev *mats) {
-    typedef typename Mode<MODE>::T T;
-    typedef typename Mode<MODE>::Acc Acc;
-    static_assert(MODE == CMP_F64 || MODE == CMP_F32, "operands in the arithmetic's own type");
-    static_assert(ST == 2 || ST == 3, "stages");
-    typedef DmaOperand<T, BM, OPA == 1> OA;
-    typedef DmaOperand<T, BN, OPB == 0> OB;
-    constexpr int E = sizeof(T), BK = OA::BK, WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wm = wave >> 1, wn = wave & 1, li = lane & 15, lk = lane >> 4;
-    const int K = p.K;
-    OA a;
-    OB b;
-    a.init(p.A, p.lda, m0, p.M, K, lane, wave);
-    b.init(p.B, p.ldb, n0, p.N, K, lane, wave);
-    lds_char *const lds = (lds_char *)&sm.b[0][0];
-    constexpr int SB = (BM + BN) * 128;  // bytes per stage
-    auto issue = [&](int c, int st) {
-        a.issue(lds + st * SB, c, wave);
-        b.issue(lds + st * SB + BM * 128, c, wave);
-    };
-    Acc acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; i++)
-#pragma unroll
-        for (int j = 0; j < TN; j++) acc[i][j] = Acc{0, 0, 0, 0};
-    // LDS offsets of this lane's operands (stage 0): of 16-row tile i at k
-    // step kk.  k-contiguous: the unit depends on kk, the tile is a constant
-    // further on; row-contiguous: the other way round.
-    constexpr int KS = BK / 4;
-    int oa[OPA == 1 ? KS : TM], ob[OPB == 0 ? KS : TN];
-#pragma unroll
-    for (int q = 0; q < (OPA == 1 ? KS : TM); q++)
-        oa[q] = OPA == 1 ? OA::at(wm * WM + li, 4 * q + lk) : OA::at(wm * WM + 16 * q + li, lk);
-#pragma unroll
-    for (int q = 0; q < (OPB == 0 ? KS : TN); q++)
-        ob[q] = BM * 128 + (OPB == 0 ? OB::at(wn * WN + li, 4 * q + lk) : OB::at(wn * WN + 16 * q + li, lk));
-    auto kstep = [&](int st, int q) {
-        T av[TM], bv[TN];
-#pragma unroll
-        for (int i = 0; i < TM; i++)
-            av[i] = *(const __attribute__((address_space(3))) T *)(lds + (OPA == 1 ? oa[q] : oa[i]) +
-                                                                   (st * SB + (OPA == 1 ? i * 16 * 128 : 4 * q * OA::RB)));
-#pragma unroll
-        for (int j = 0; j < TN; j++)
-            bv[j] = *(const __attribute__((address_space(3))) T *)(lds + (OPB == 0 ? ob[q] : ob[j]) +
-                                                                   (st * SB + (OPB == 0 ? j * 16 * 128 : 4 * q * OB::RB)));
-#pragma unroll
-        for (int i = 0; i < TM; i++)
-#pragma unroll
-            for (int j = 0; j < TN; j++) {
-                if constexpr (MODE == CMP_F64)
-                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(bv[j], av[i], acc[i][j], 0, 0, 0);
-                else
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[j], av[i], acc[i][j], 0, 0, 0);
-            }
-    };
-    // chunks whose products are all zero by the operands' triangular
-    // structure are skipped, as in gemm_tile_op
-    const int klo = max((p.ktri & 1) ? (p.cpx ? 2 * n0 : n0) : 0, (p.ktri & 2) ? m0 : 0);
-    const int nch = (K + BK - 1) / BK, nfull = K / BK, c0 = min(klo / BK, nch);
-    constexpr int NI = OA::NI + OB::NI;  // loads per wavefront and chunk
-    if (c0 < nch) issue(c0, 0);
-    if constexpr (ST == 3) {
-        if (c0 + 1 < nch) issue(c0 + 1, 1);
-    }
-    // chunk c (stage S) has landed everywhere and chunk c - 1 is used up
-    auto arrive = [&](int c, int S) {
-        if (ST == 3 && c + 1 < nch)
-            dma_barrier<(ST == 3 ? NI : 0)>();
-        else
-            dma_barrier<0>();
-        if (c + ST - 1 < nch) issue(c + ST - 1, (S + ST - 1) % ST);
-    };
-    auto step = [&](int c, auto S_) {
-        constexpr int S = decltype(S_)::value;
-        arrive(c, S);
-#pragma unroll
-        for (int q = 0; q < KS; q++) kstep(S, q);
-    };
-    typedef std::integral_constant<int, 0> S0;
-    typedef std::integral_constant<int, 1> S1;
-    typedef std::integral_constant<int, ST - 1> SL;
-    for (int c = c0; c < nfull; c += ST) {
-        step(c, S0{});
-        if (c + 1 < nfull) step(c + 1, S1{});
-        if constexpr (ST == 3) {
-            if (c + 2 < nfull) step(c + 2, SL{});
-        }
-    }
-    if (max(c0, nfull) < nch) {
-        // last, partial chunk
-        const int S = max(nfull - c0, 0) % ST;
-        arrive(nch - 1, S);
-        const int kr = K - nfull * BK, nz = (4 - (kr & 3)) & 3;
-        for (int e = threadIdx.x; e < nz * (BM + BN); e += 256) {
-            const int k = kr + e / (BM + BN), r = e % (BM + BN);
-            const int o = r < BM ? OA::at(r, k) : BM * 128 + OB::at(r - BM, k);
-            *(__attribute__((address_space(3))) T *)(lds + S * SB + o) = (T)0;
-        }
-        dma_barrier<0>();
-#pragma unroll
-        for (int q = 0; q < KS; q++)
-            if (4 * q < kr) kstep(S, q);
-    }
-    gemm_store<MODE, BM, BN, TC, CIN, PUSH, TG>(p, m0, n0, acc, mats);
+    AccTile<MODE, BM, BN> t;
+    DmaProduct<MODE, BM, BN, ST, OPA, OPB>::form(p, m0, n0, sm, t);
+    gemm_store<MODE, BM, BN, TC, CIN, PUSH, TG>(p, m0, n0, t.a, mats);
 }
 
 template <int MODE, int BM, int BN, int ST, typename TC, bool CIN, bool PUSH = false>
