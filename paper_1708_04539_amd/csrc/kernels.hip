@@ -13,6 +13,8 @@
 //   extract_kernel   step 6: the selected entries, one per entry of A.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "device_types.hpp"
 #include "kernels.hpp"
 #include "tiles.hpp"
@@ -37,32 +39,37 @@ namespace selinv {
 // NB = 4 handles every 64-wide sub-block; NB = 1 and 2 (16- and 32-wide
 // blocks, far less LDS) serve the supernodes of at most 16 or 32 columns
 // whose normalisation runs in the same workgroup.
+// Bound by the latency of a chain of small steps (load, substitution, up to 40
+// dependent MFMAs, stores), so by how many workgroups share a compute unit.
+// With a second LDS tile for the factors and the staged panels (76 KB, two
+// workgroups) the 5683 leaf blocks of 12 grids of side 64-256 took 288 us; in
+// place and with the panels in registers (33 KB, 108 VGPRs, four) 154 us, and
+// the two launches of the 2D 256^2 matrix 102 -> 69 us.
 // Normalisation and diagonal initialisation of a supernode with s, c_L,
-// c_U <= 64, after its inverses are complete in sm.Xs (FP64 arithmetic on
+// c_U <= 64, after its inverses are complete in LDS (FP64 arithmetic on
 // v_mfma_f64_16x16x4, results in the storage precision).  Every product is
 // formed transposed (the MFMA takes the inverse as its first operand), so
 // that a lane's results run down a column of the output and the stores are
-// coalesced.  The panels are staged through sm.Ds, free after the rounds.
+// coalesced.  Wavefront w takes rows 16 w .. of the panels and reads them
+// straight into its operand registers (16 rows of one column are 128
+// consecutive bytes), the L panel before the inversion's rounds, so that the
+// rounds hide its latency.
 template <int NB>
-__device__ __forceinline__ void tri_fused_epilogue(TriSmem<NB> &sm, const TriItem &it, int lane, int wave) {
-    const int s = it.s, li = lane & 15, lk = lane >> 4;
-    const int nbs = (s + 15) / 16;
-    auto stage = [&](const double *pan, int rows) {
-        // Ds[k][m] = pan(m, k), zero outside rows x s
+struct TriPanel {
+    double v[4 * NB];  // pan(16 w + lane % 16, 4 q + lane / 16)
+    __device__ __forceinline__ void load(const double *pan, int rows, int s, int lane, int wave) {
+        if (!pan || 16 * wave >= rows) return;
         const SELINV_GLOBAL double *P = gptr(pan);
-        const int r = lane, rr = min(r, rows - 1);
-        double v[4 * NB];
+        const int m = min(16 * wave + (lane & 15), rows - 1);
 #pragma unroll
-        for (int q = 0; q < 4 * NB; q++) {
-            const int c = wave + 4 * q;
-            v[q] = P[(int64_t)rr + (int64_t)min(c, s - 1) * rows];
-        }
-#pragma unroll
-        for (int q = 0; q < 4 * NB; q++) {
-            const int c = wave + 4 * q;
-            sm.Ds[c][r] = (r < rows && c < s) ? v[q] : 0.0;
-        }
-    };
+        for (int q = 0; q < 4 * NB; q++) v[q] = P[m + (int64_t)min(4 * q + (lane >> 4), s - 1) * rows];
+    }
+};
+
+template <int NB>
+__device__ __forceinline__ void tri_fused_epilogue(TriSmem<NB> &sm, const TriItem &it, TriPanel<NB> &lp, int lane,
+                                                   int wave) {
+    const int s = it.s, li = lane & 15, lk = lane >> 4;
     auto put = [&](void *out, int64_t idx, double v) {
         if (it.f32out)
             gptr_w((float *)out)[idx] = (float)v;
@@ -70,47 +77,63 @@ __device__ __forceinline__ void tri_fused_epilogue(TriSmem<NB> &sm, const TriIte
             gptr_w((double *)out)[idx] = v;
     };
     // panel products: out(m, n) = sum_k pan(m, k) inv(k, n), inv(k, n) =
-    // Linv(k, n) (L side) or Uinv(n, k) (U side)
-    auto panel = [&](const double *pan, int rows, void *out, bool upper) {
-        __syncthreads();  // Ds free (rounds done / previous panel read)
-        stage(pan, rows);
-        __syncthreads();
-        const int mbs = (rows + 15) / 16;
-        for (int t = wave; t < mbs * nbs; t += 4) {
-            const int mb = t % mbs, nb = t / mbs;
-            v4d_t acc = {0, 0, 0, 0};
-            for (int kk = 0; kk < s; kk += 4) {
-                const int k = kk + lk;
-                const double a = upper ? uinv_at(sm, 16 * nb + li, k) : linv_at(sm, k, 16 * nb + li);
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, sm.Ds[k][16 * mb + li], acc, 0, 0, 0);
+    // Linv(k, n) (L side) or Uinv(n, k) (U side), zero for k < n
+    auto panel = [&](const TriPanel<NB> &pan, int rows, void *out, auto UPPER_) {
+        constexpr bool UPPER = decltype(UPPER_)::value;
+        if (16 * wave >= rows) return;
+        v4d acc[NB];
+#pragma unroll
+        for (int nb = 0; nb < NB; nb++) acc[nb] = v4d{0, 0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < 4 * NB; q++) {
+            if (4 * q >= s) break;
+            const int k = 4 * q + lk;
+            const double p = k < s ? pan.v[q] : 0.0;
+#pragma unroll
+            for (int nb = 0; nb < NB; nb++) {
+                if (16 * nb > 4 * q + 3) continue;
+                const int n = 16 * nb + li;
+                acc[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(UPPER ? uinv_at(sm, n, k) : linv_at(sm, k, n), p,
+                                                               acc[nb], 0, 0, 0);
             }
-            // acc[v] = out(16 mb + li, 16 nb + lk + 4 v)
-            const int m = 16 * mb + li;
+        }
+        // acc[nb][v] = out(16 w + li, 16 nb + lk + 4 v)
+        const int m = 16 * wave + li;
+#pragma unroll
+        for (int nb = 0; nb < NB; nb++)
 #pragma unroll
             for (int v = 0; v < 4; v++) {
                 const int n = 16 * nb + lk + 4 * v;
-                if (m < rows && n < s) put(out, m + (int64_t)n * rows, acc[v]);
+                if (m < rows && n < s) put(out, m + (int64_t)n * rows, acc[nb][v]);
             }
-        }
     };
-    if (it.lpan) panel(it.lpan, it.cl, it.Lh, false);
-    if (it.upan) panel(it.upan, it.cu, it.Uh, true);
-    // A^{-T}(K,K) := Linv^T Uinv^T:  Zd(m, n) = sum_k Linv(k, m) Uinv(n, k)
+    TriPanel<NB> up;
+    up.load(it.upan, it.cu, s, lane, wave);
+    if (it.lpan) panel(lp, it.cl, it.Lh, std::false_type{});
+    if (it.upan) panel(up, it.cu, it.Uh, std::true_type{});
+    // A^{-T}(K,K) := Linv^T Uinv^T:  Zd(m, n) = sum_k Linv(k, m) Uinv(n, k),
+    // k >= max(m, n); wavefront w takes rows 16 w ..
     SELINV_GLOBAL double *Zd = gptr_w(it.Zd);
-    for (int t = wave; t < nbs * nbs; t += 4) {
-        const int mb = t % nbs, nb = t / nbs;
-        v4d_t acc = {0, 0, 0, 0};
-        for (int kk = 0; kk < s; kk += 4) {
-            const int k = kk + lk;
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(uinv_at(sm, 16 * nb + li, k), linv_at(sm, k, 16 * mb + li),
-                                                       acc, 0, 0, 0);
-        }
-        const int m = 16 * mb + li;
+    if (wave < NB && 16 * wave < s) {
+        const int m = 16 * wave + li;
+        v4d acc[NB];
 #pragma unroll
-        for (int v = 0; v < 4; v++) {
-            const int n = 16 * nb + lk + 4 * v;
-            if (m < s && n < s) Zd[m + (int64_t)n * s] = acc[v];
+        for (int nb = 0; nb < NB; nb++) acc[nb] = v4d{0, 0, 0, 0};
+        for (int kk = 16 * wave; kk < s; kk += 4) {
+            const int k = kk + lk;
+            const double l = linv_at(sm, k, m);
+#pragma unroll
+            for (int nb = 0; nb < NB; nb++)
+                if (16 * nb <= kk + 3)
+                    acc[nb] = __builtin_amdgcn_mfma_f64_16x16x4f64(uinv_at(sm, 16 * nb + li, k), l, acc[nb], 0, 0, 0);
         }
+#pragma unroll
+        for (int nb = 0; nb < NB; nb++)
+#pragma unroll
+            for (int v = 0; v < 4; v++) {
+                const int n = 16 * nb + lk + 4 * v;
+                if (m < s && n < s) Zd[m + (int64_t)n * s] = acc[nb][v];
+            }
     }
 }
 
@@ -134,15 +157,17 @@ __device__ __forceinline__ void tri_base_item(const TriItem &it, TriSmem<NB> &sm
             const int e = tid + 256 * q, r = e % W, c = e / W;
             if (e >= W * W) continue;
             const double d = (r < b && c < b) ? v[q] : (r == c ? 1.0 : 0.0);
-            sm.Ds[c][r] = d;
+            sm.M[c][r] = d;
             if (r == c) sm.rd[c] = 1.0 / d;
         }
     }
     __syncthreads();
+    TriPanel<NB> lp;
+    if (it.fused) lp.load(it.lpan, it.cl, s, lane, wave);
     tri_invert<NB>(sm, lane, wave);
     __syncthreads();
     if (it.fused) {
-        tri_fused_epilogue<NB>(sm, it, lane, wave);
+        tri_fused_epilogue<NB>(sm, it, lp, lane, wave);
         return;
     }
     if constexpr (NB == 4) {
@@ -176,8 +201,7 @@ __global__ __launch_bounds__(256) void tri_base_kernel(const TriItem *__restrict
 
 // Items [0, count), item b + q gridDim.x to workgroup b: a launch with fewer
 // workgroups than items keeps at most that many resident (the side-stream
-// inversion of the leaves, beside the level chain: one 64-wide workgroup takes
-// half the LDS of a compute unit).  The item is a call: inlined into the
+// inversion of the leaves, beside the level chain).  The item is a call: inlined into the
 // loop, the item's per-lane LDS addresses are hoisted out of it and held
 // across iterations, which more than triples the kernel's registers.
 template <int NB>
@@ -187,7 +211,7 @@ __device__ __attribute__((noinline)) void tri_base_item_call(const TriItem *__re
 }
 
 template <int NB>
-__global__ __launch_bounds__(256) void tri_base_loop_kernel(const TriItem *__restrict__ items, int count) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void tri_base_loop_kernel(const TriItem *__restrict__ items, int count) {
     __shared__ TriSmem<NB> sm;
     for (int b = blockIdx.x; b < count; b += gridDim.x) {
         tri_base_item_call<NB>(items, b, sm);

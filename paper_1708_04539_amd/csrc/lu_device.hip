@@ -50,7 +50,7 @@ __global__ __launch_bounds__(256) void scatter_values_kernel(const int64_t *__re
     gptr_w(dst)[off] = v;
 }
 
-// LU of the 16 nb wide block in sm.Ds (identity-padded) by one workgroup, in
+// LU of the 16 nb wide block in sm.M (identity-padded) by one workgroup, in
 // 16-column panels: one wavefront eliminates the panel with lane i holding row
 // i of it in registers (the pivot row reaches the other lanes through scalar
 // registers, v_readlane), the other three form the rows of U right of it, 16
@@ -71,7 +71,7 @@ __device__ __forceinline__ void lu_factor_block(SM &sm, int nb, int lane, int wa
         if (wave == 0) {
             double a[16];
 #pragma unroll
-            for (int c = 0; c < 16; c++) a[c] = sm.Ds[k0 + c][lane];
+            for (int c = 0; c < 16; c++) a[c] = sm.M[k0 + c][lane];
             // the reciprocal of the next pivot is formed as soon as its column is
             // updated, beside the updates of the other columns
             double rp = 1.0 / lane_value(a[0], k0);
@@ -92,16 +92,16 @@ __device__ __forceinline__ void lu_factor_block(SM &sm, int nb, int lane, int wa
             }
             if (lane > k0 + 15) a[15] *= rp;
 #pragma unroll
-            for (int c = 0; c < 16; c++) sm.Ds[k0 + c][lane] = a[c];
+            for (int c = 0; c < 16; c++) sm.M[k0 + c][lane] = a[c];
         }
         __syncthreads();
         if (kb + 1 == nb) break;
         if (wave > 0 && lane < 16 && kb + wave < nb) {  // block column kb + wave
             double m[16], x[16];  // row `lane` of the panel's unit L, column `lane` of the block
-            double *col = sm.Ds[k0 + 16 * wave + lane];
+            double *col = sm.M[k0 + 16 * wave + lane];
 #pragma unroll
             for (int r = 0; r < 16; r++) {
-                m[r] = sm.Ds[k0 + r][k0 + lane];
+                m[r] = sm.M[k0 + r][k0 + lane];
                 x[r] = col[k0 + r];
             }
             tri_substitute<0, false>(m, x, 1.0);
@@ -112,15 +112,15 @@ __device__ __forceinline__ void lu_factor_block(SM &sm, int nb, int lane, int wa
         const int nt = nb - kb - 1;
         for (int t = wave; t < nt * nt; t += 4) {
             const int i = k0 + 16 + 16 * (t % nt), j = k0 + 16 + 16 * (t / nt);
-            v4d_t acc;
+            v4d acc;
 #pragma unroll
-            for (int v = 0; v < 4; v++) acc[v] = sm.Ds[j + li][i + lk + 4 * v];
+            for (int v = 0; v < 4; v++) acc[v] = sm.M[j + li][i + lk + 4 * v];
 #pragma unroll
             for (int kk = 0; kk < 16; kk += 4)
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-sm.Ds[k0 + kk + lk][i + li], sm.Ds[j + li][k0 + kk + lk],
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-sm.M[k0 + kk + lk][i + li], sm.M[j + li][k0 + kk + lk],
                                                            acc, 0, 0, 0);
 #pragma unroll
-            for (int v = 0; v < 4; v++) sm.Ds[j + li][i + lk + 4 * v] = acc[v];
+            for (int v = 0; v < 4; v++) sm.M[j + li][i + lk + 4 * v] = acc[v];
         }
         __syncthreads();
     }
@@ -152,20 +152,20 @@ __global__ __launch_bounds__(256) void lu_tile_kernel(const LuTile *__restrict__
 #pragma unroll
         for (int q = 0; q < 16; q++) {
             const int c = wave + 4 * q;
-            sm.Ds[c][lane] = (lane < b && c < b) ? v[q] : (lane == c ? 1.0 : 0.0);
+            sm.M[c][lane] = (lane < b && c < b) ? v[q] : (lane == c ? 1.0 : 0.0);
         }
     }
     __syncthreads();
     lu_factor_block(sm, nb, lane, wave);
     if (tid < 64) {
-        const double p = sm.Ds[tid][tid];
+        const double p = sm.M[tid][tid];
         sm.rd[tid] = 1.0 / p;
         if (tid < b && !(p != 0.0 && isfinite(p))) atomicMin(bad, it.f + it.j0 + tid);
     }
 #pragma unroll
     for (int q = 0; q < 16; q++) {
         const int c = wave + 4 * q;
-        if (lane < b && c < b) D[lane + (int64_t)c * s] = sm.Ds[c][lane];
+        if (lane < b && c < b) D[lane + (int64_t)c * s] = sm.M[c][lane];
     }
     __syncthreads();
     if (nb > 2)
