@@ -552,11 +552,55 @@ int add_prob(std::vector<GemmProb> &probs, const void *A, int opA, int lda,
 
 GatherTile gather_tile_of(selinv_handle h, int32_t mi, int32_t K, int a0, int b0, int32_t skip);
 selinv_status ensure_codes_all(selinv_handle h);
+bool all_coded(selinv_handle h);
 
 // A supernode whose diagonal block, R_L and R_U all fit one 64-wide tile has
 // its normalisation and diagonal initialisation done by the workgroup that
 // inverts its diagonal block (tri_base_kernel), from the inverses in LDS.
 inline bool fused_prologue(const SnRec &r) { return r.s <= 64 && r.cl <= 64 && r.cu <= 64; }
+
+// Levels whose steps 3/5 read G_K from its sources without a tuning: only where
+// every G_K of the plan has gather codes (their merge takes microseconds), and
+// where a stored G gains nothing from being read again, that is where the
+// products read it once (s up to one tile).  A launch of 32-wide tiles waits
+// for its loads either way, and the gather and the push it saves count; FP64
+// levels gain up to s = 128.  A launch of 64-wide tiles gains while the products
+// are thin (s <= 32) or G_K small (tiles of the gather mostly edges).  Time of
+// the level with the step-4 launch above it, in place / stored: 2D 256^2 FP64
+// levels of 32-wide tiles 0.82-0.98 (s = 128 .. 16), mixed FP32 193x117
+// 0.84-0.99, but split-BF16 24^3 1.08-1.30 at s = 72 .. 200; complex 256^2
+// 64-wide tiles 0.79-0.88 (s = 16, 32), a batch of 12 grids 0.90-0.96 (c up to
+// 78, s = 49 .. 64) and 1.01-1.06 (c from 98, s = 64).
+std::vector<char> in_place_levels(const std::vector<selinv_handle> &hs, int prec) {
+    int depth = 0;
+    for (auto h : hs) {
+        depth = std::max(depth, h->P.nlevels);
+        if (!all_coded(h)) return {};
+    }
+    std::vector<char> use(depth, 0);
+    for (int d = 0; d < depth; d++) {
+        double t64 = 0, g = 0, n = 0;
+        int smax = 0;
+        for (auto h : hs) {
+            if (d >= h->P.nlevels) continue;
+            for (int32_t K : h->P.levels[d]) {
+                const SnRec &r = h->sn[K];
+                if (r.cl == 0 && r.cu == 0) continue;
+                const double sc = h->cpx_ok ? r.s / 2 : r.s;  // columns formed by the products
+                t64 += std::ceil(sc / 64) * (std::ceil(r.cl / 64.0) + std::ceil(r.cu / 64.0));
+                g += (double)r.cl * r.cu;
+                n += 1;
+                smax = std::max(smax, r.s);
+            }
+        }
+        if (n == 0) continue;
+        if (t64 < kTile32Below)
+            use[d] = smax <= (prec == SELINV_FP64 ? 128 : 64);
+        else
+            use[d] = smax <= 32 || (smax <= 64 && g <= 6500 * n);
+    }
+    return use;
+}
 
 // Build the work lists of one sweep over a set of factored handles.
 selinv_status build_sweep(std::vector<selinv_handle> &hs, const DevAlloc &al, int prec, int sweep_mode,
@@ -571,7 +615,12 @@ selinv_status build_sweep(std::vector<selinv_handle> &hs, const DevAlloc &al, in
     // choice), in a level sweep only (the persistent sweep gathers), and
     // never a level of the fused small-supernode launch (decided below).
     bool vg_ok = sweep_mode != SWEEP_PERSISTENT;
+    // Without a tuning (form 0): the levels where reading G_K in place was
+    // measured faster, if the codes are there (in_place_levels).
+    const std::vector<char> vg_policy =
+        gather_form == 0 && !tn && vg_ok ? in_place_levels(hs, prec) : std::vector<char>();
     auto vg_wanted = [&](int d) {
+        if (gather_form == 0 && !tn) return d < (int)vg_policy.size() && vg_policy[d] != 0;
         return gather_form == 2 || (gather_form == 0 && tn && d < (int)tn->vg.size() && tn->vg[d]);
     };
     {
@@ -1542,9 +1591,17 @@ void build_gather_codes(const Plan &P, std::vector<SnRec> &sn, std::vector<uint3
     }
 }
 
+// Every non-empty G_K has gather codes (gcL, gcU).
+bool all_coded(selinv_handle h) {
+    for (const SnRec &r : h->sn)
+        if (r.cl > 0 && r.cu > 0 && r.c_off < 0) return false;
+    return true;
+}
+
 // The codes of every G_K in its own layout (MatDev::gcA), built once per
-// handle on first use: filled by up to 16 host threads over the supernodes,
-// uploaded, and the host copy released.
+// handle on first use: merged on the device where every G_K has gather codes,
+// else filled by up to 16 host threads over the supernodes, uploaded, and the
+// host copy released.
 selinv_status ensure_codes_all(selinv_handle h) {
     if (h->ca_state != 0) return SELINV_OK;
     const Plan &P = h->P;
@@ -1560,6 +1617,15 @@ selinv_status ensure_codes_all(selinv_handle h) {
         if (cl == 0 || cu == 0) continue;
         h->ca_off[K] = used;
         used += cl * cu;
+    }
+    if (used > 0 && used == (int64_t)h->gcL.size() && all_coded(h)) {
+        // the same order and offsets: ca_off(K) = c_off(K)
+        HIPCHK(h->err, alloc_bytes(h->al, (void **)&h->d_gcA, used * sizeof(uint32_t)), "alloc gather codes");
+        HIPCHK(h->err, launch_merge_codes(h->d_sn, P.ns, h->d_gcL, h->d_gcU, h->d_gcA, nullptr), "merge gather codes");
+        HIPCHK(h->err, hipStreamSynchronize(nullptr), "merge gather codes");
+        h->ca_total = used;
+        h->ca_state = 1;
+        return SELINV_OK;
     }
     std::vector<uint32_t> codes;
     try {

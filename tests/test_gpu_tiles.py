@@ -141,3 +141,34 @@ def test_policy_sweep_equals_plain_levels(dims, cap, prec):
         s.run(prec, stream=st)
         _, _, y = s.export(sort=False)
         assert np.array_equal(x, y)
+
+
+# G_K read in place by the level sweep's own choice (no tuning) against a stored
+# G: the sides of the choice (s and c around one tile, 32- and 64-wide tiles,
+# plans with and without codes for every G_K)
+@pytest.mark.parametrize("dims,cap,budget", [((9, 7), 16, -1), ((64, 64), 64, -1), ((128, 96), 130, -1),
+                                             ((200, 200), 32, -1), ((64, 64), 64, 0), ((64, 64), 64, 5000)],
+                         ids=["9x7", "64x64", "128x96", "200x200", "64x64-maps", "64x64-some"])
+@pytest.mark.parametrize("prec", ["fp64", "mixed_fp32", "mixed_bf16x3"])
+def test_policy_in_place_levels(dims, cap, budget, prec):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_1708_04539_amd import selinv as si
+    from workloads import config_grid
+    print("[case] in-place levels", dims, cap, budget, prec, flush=True)
+    w = config_grid("p", dims, "box", "sym_perturbed", 0.1, 3, cap, 32, delta=0.15)
+    s = si.SelInv(w.n, w.colptr, w.rowind, w.perm, w.max_super, w.relax, w.pad_pct)
+    s.set_gather_code_budget(budget)
+    s.factor(w.values)
+    s.run(prec)
+    _, _, x = s.export(sort=False)
+    L = s.info["nlevels"]
+    in_place = [d for d in range(L) if s.level_stats(d)["gather_fused"] == 2]
+    # (9x7: every level is made of small supernodes and keeps G_K in LDS)
+    assert bool(in_place) == (budget < 0 and dims != (9, 7))
+    s.set_gather_form("stored")
+    s.run(prec)
+    assert not any(s.level_stats(d)["gather_fused"] == 2 for d in range(L))
+    _, _, y = s.export(sort=False)
+    assert np.array_equal(x, y)
