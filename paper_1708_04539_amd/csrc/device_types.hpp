@@ -30,7 +30,7 @@ struct MatDev {
     const double *Zd;  // A^{-T} diagonal blocks (FP64 in every form)
     const void *ZL;    // A^{-T}(R_L, K) panels, FP64 or FP32
     const void *ZU;    // A^{-T}(K, R_U)^T panels, FP64 or FP32
-    void *G;           // gather workspace, FP64 or FP32
+    void *G;           // gather workspace, FP64, FP32 or split-BF16 words
     // children of every supernode (kids[kids_ptr[P] .. kids_ptr[P+1])), and
     // for a child K of P the positions of P's columns in R_L(K) and R_U(K):
     // push_pos[push_off[K] + r] = a with R_L(K)[a] = first(P) + r (or -1),
@@ -119,7 +119,7 @@ struct TriItem {
     // Uhat = U(K,R_U)^T U_KK^{-T} (c_U x s) and A^{-T}(K,K) := L_KK^{-T}
     // U_KK^{-T} from the inverses in LDS; Linv / Uinv are then not stored
     const double *lpan, *upan;
-    void *Lh, *Uh;  // FP64, or FP32 when f32out
+    void *Lh, *Uh;  // FP64, FP32 (f32out 1) or split-BF16 words (f32out 2)
     double *Zd;
     int32_t cl, cu, f32out, fused;
 };
@@ -136,8 +136,8 @@ struct SmallItem {
 // split-K of a step-4 product: C(M x N, ld ldc) += sum of nparts partial
 // products P[p * pstride + m + n M], added in order p = 0, 1, ...; with
 // push_sn >= 0 the final entries also go into G of that supernode's children
-// (as the push of an unsplit step-4 product, see GemmProb), G in FP32 when
-// g_f32
+// (as the push of an unsplit step-4 product, see GemmProb), G in FP32 (g_f32
+// 1) or split-BF16 words (g_f32 2)
 struct ReduceItem {
     double *C;
     const double *P;

@@ -36,12 +36,12 @@ template <int MODE, int BM>
 struct DmaStages {
     static constexpr int value = 2;
 };
-// Tiles of a product that take gemm_tile_dma: operands in the arithmetic's
-// own type, 64 wide (FP32 also 128 wide; 128-wide FP64 tiles leave it no
-// registers).  The 32-wide tiles serve launches that wait for their loads, not
-// for the matrix pipe.
+// Tiles of a product that take gemm_tile_dma: both operands in the type of the
+// arrays that only products read, 64 wide (FP32 and split-BF16 also 128 wide;
+// 128-wide FP64 tiles leave it no registers).  The 32-wide tiles serve launches
+// that wait for their loads, not for the matrix pipe.
 template <int MODE, int BM, typename TA>
-constexpr bool kDmaTile = (BM == 64 || (BM == 128 && MODE == CMP_F32)) && MODE != CMP_BF16X3 && std::is_same<TA, typename Mode<MODE>::T>::value;
+constexpr bool kDmaTile = (BM == 64 || (BM == 128 && MODE != CMP_F64)) && std::is_same<TA, typename Mode<MODE>::G>::value;
 
 // ROLE only names the launch site in profiles (0: triangular inversion,
 // normalisation and diagonal initialisation; 1: products of steps 3 and 5;
@@ -51,6 +51,8 @@ constexpr bool kDmaTile = (BM == 64 || (BM == 128 && MODE == CMP_F32)) && MODE !
 template <int MODE, int BM, int BN, typename TA, typename TC, int ROLE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BM == 128 ? 2 : 4))) void gemm_v2(const GemmProb *__restrict__ probs,
                                                const GemmTile *__restrict__ tiles) {
+    // op(B) is a normalised panel, but in the prologue's products
+    typedef std::conditional_t<ROLE == 0, TA, typename Mode<MODE>::G> TB;
     constexpr bool D = kDmaTile<MODE, BM, TA>;
     typedef std::conditional_t<D, DmaSmem<BM, BN, DmaStages<MODE, BM>::value>, Smem<MODE, BM, BN>> SM;
     __shared__ SM sm;
@@ -60,7 +62,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BM == 128 ?
         if constexpr (D)
             gemm_tile_dma<MODE, BM, BN, DmaStages<MODE, BM>::value, TC, ROLE == 2>(probs[tl.prob], tl.m0, n0, sm);
         else
-            gemm_tile<MODE, BM, BN, TA, TC, ROLE == 2>(probs[tl.prob], tl.m0, n0, sm);
+            gemm_tile<MODE, BM, BN, TA, TB, TC, ROLE == 2>(probs[tl.prob], tl.m0, n0, sm);
     };
     tile(tl.n0);
     if (tl.n1 > 0) {
@@ -138,10 +140,11 @@ __global__ __launch_bounds__(256) void step4_gather(const GemmProb *__restrict__
             gemm_tile_dma<MODE, BM, BN, DmaStages<MODE, BM>::value, double, true, true>(probs[tl.prob], tl.m0, tl.n0,
                                                                                        sm.g, mats);
         else
-            gemm_tile<MODE, BM, BN, TA, double, true, true>(probs[tl.prob], tl.m0, tl.n0, sm.g, mats);
+            gemm_tile<MODE, BM, BN, TA, typename Mode<MODE>::G, double, true, true>(probs[tl.prob], tl.m0, tl.n0,
+                                                                                     sm.g, mats);
     } else {
         const GatherTile gt = gtiles[b - ntiles];
-        gather_tile<TA>(mats[gt.mat], gt, sm.t);
+        gather_tile<TA, typename Mode<MODE>::G>(mats[gt.mat], gt, sm.t);
     }
 }
 
@@ -187,7 +190,7 @@ hipError_t launch_gemm(int role, int mode, int tile, const GemmProb *probs, cons
             if (mode == CMP_F32)
                 launch_mode<CMP_F32, double, float, 0>(tile, probs, tiles, ntiles, st);
             else if (mode == CMP_BF16X3)
-                launch_mode<CMP_BF16X3, double, float, 0>(tile, probs, tiles, ntiles, st);
+                launch_mode<CMP_BF16X3, double, Pk32, 0>(tile, probs, tiles, ntiles, st);
             else
                 return hipErrorInvalidValue;
             break;
@@ -200,7 +203,7 @@ hipError_t launch_gemm(int role, int mode, int tile, const GemmProb *probs, cons
             else if (mode == CMP_F32)
                 launch_mode<CMP_F32, float, float, 1>(tile, probs, tiles, ntiles, st);
             else if (mode == CMP_BF16X3)
-                launch_mode<CMP_BF16X3, float, float, 1>(tile, probs, tiles, ntiles, st);
+                launch_mode<CMP_BF16X3, Pk32, float, 1>(tile, probs, tiles, ntiles, st);
             else
                 return hipErrorInvalidValue;
             break;

@@ -72,7 +72,9 @@ __device__ __forceinline__ void tri_fused_epilogue(TriSmem<NB> &sm, const TriIte
                                                    int wave) {
     const int s = it.s, li = lane & 15, lk = lane >> 4;
     auto put = [&](void *out, int64_t idx, double v) {
-        if (it.f32out)
+        if (it.f32out == 2)
+            gptr_w((uint32_t *)out)[idx] = stored<Pk32>(v);
+        else if (it.f32out)
             gptr_w((float *)out)[idx] = (float)v;
         else
             gptr_w((double *)out)[idx] = v;
@@ -223,12 +225,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void t
 // ---------------------------------------------------------------------------
 // gather
 // ---------------------------------------------------------------------------
-template <typename T>
+template <typename T, typename TG>
 __global__ __launch_bounds__(256) void gather_kernel(const MatDev *__restrict__ mats,
                                                      const GatherTile *__restrict__ tiles) {
     __shared__ GatherSmem<T> sm;
     const GatherTile tl = tiles[blockIdx.x];
-    gather_tile<T>(mats[tl.mat], tl, sm);
+    gather_tile<T, TG>(mats[tl.mat], tl, sm);
 }
 
 // The two source-code arrays of the gather (MatDev::gcL in G's column order,
@@ -301,7 +303,9 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceItem *__
             if (a < 0 || b < 0) continue;
             const double v = h ? csign * acc : acc;
             const int64_t g = sn[K].g_off + a + (int64_t)b * sn[K].cl;
-            if (it.g_f32)
+            if (it.g_f32 == 2)
+                gptr_w((uint32_t *)Md.G)[g] = stored<Pk32>(v);
+            else if (it.g_f32)
                 gptr_w((float *)Md.G)[g] = (float)v;
             else
                 gptr_w((double *)Md.G)[g] = v;
@@ -352,12 +356,14 @@ hipError_t launch_tri_base(const TriItem *items, int count, int nb, hipStream_t 
     return hipGetLastError();
 }
 
-hipError_t launch_gather(int f64, const MatDev *mats, const GatherTile *tiles, int ntiles, hipStream_t st) {
+hipError_t launch_gather(int mode, const MatDev *mats, const GatherTile *tiles, int ntiles, hipStream_t st) {
     if (ntiles <= 0) return hipSuccess;
-    if (f64)
-        hipLaunchKernelGGL(gather_kernel<double>, dim3(ntiles), dim3(256), 0, st, mats, tiles);
+    if (mode == CMP_F64)
+        hipLaunchKernelGGL((gather_kernel<double, double>), dim3(ntiles), dim3(256), 0, st, mats, tiles);
+    else if (mode == CMP_F32)
+        hipLaunchKernelGGL((gather_kernel<float, float>), dim3(ntiles), dim3(256), 0, st, mats, tiles);
     else
-        hipLaunchKernelGGL(gather_kernel<float>, dim3(ntiles), dim3(256), 0, st, mats, tiles);
+        hipLaunchKernelGGL((gather_kernel<float, Pk32>), dim3(ntiles), dim3(256), 0, st, mats, tiles);
     return hipGetLastError();
 }
 

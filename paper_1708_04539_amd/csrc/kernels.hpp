@@ -31,7 +31,7 @@ enum : int {
 // GEMM_TILE_64 or GEMM_TILE_128 (the tile list must use the same size)
 hipError_t launch_gemm(int role, int mode, int tile, const GemmProb *probs, const GemmTile *tiles, int ntiles,
                        hipStream_t st);
-hipError_t launch_gather(int f64, const MatDev *mats, const GatherTile *tiles, int ntiles, hipStream_t st);
+hipError_t launch_gather(int mode, const MatDev *mats, const GatherTile *tiles, int ntiles, hipStream_t st);
 // steps 3 and 5 with G_K read from its sources through the codes of
 // mats[p.gmat].gcA (every problem has gcode >= 0 and opB = 0), results in the
 // storage precision of the mode (gemm.hip)

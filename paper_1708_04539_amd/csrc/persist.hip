@@ -53,6 +53,7 @@ __device__ inline void wait_geq(const int32_t *p, int32_t target, int32_t *err) 
 template <int MODE>
 __global__ __launch_bounds__(256) void sweep_kernel(const PersistArgs a) {
     typedef typename Mode<MODE>::T T;
+    typedef typename Mode<MODE>::G G;
     union Shared {
         Smem<MODE, 64, 64> g;
         GatherSmem<T> t;
@@ -81,11 +82,11 @@ __global__ __launch_bounds__(256) void sweep_kernel(const PersistArgs a) {
         }
         __syncthreads();
         if (tk.type == PT_GATHER)
-            gather_tile<T>(a.mats[tk.mat], gather_desc(a.mats[tk.mat], tk.mat, tk.K, tk.i0, tk.i1), sm.t);
+            gather_tile<T, G>(a.mats[tk.mat], gather_desc(a.mats[tk.mat], tk.mat, tk.K, tk.i0, tk.i1), sm.t);
         else if (tk.type == PT_STEP35)
-            gemm_tile<MODE, 64, 64, T, T, false>(a.probs[tk.prob], tk.i0, tk.i1, sm.g);
+            gemm_tile<MODE, 64, 64, G, G, T, false>(a.probs[tk.prob], tk.i0, tk.i1, sm.g);
         else
-            gemm_tile<MODE, 64, 64, T, double, true>(a.probs[tk.prob], tk.i0, tk.i1, sm.g);
+            gemm_tile<MODE, 64, 64, T, G, double, true>(a.probs[tk.prob], tk.i0, tk.i1, sm.g);
         __syncthreads();  // every thread's stores of this task are complete
         if (threadIdx.x == 0) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
@@ -188,22 +189,17 @@ struct SplitB {
     v8bf h[2], l[2];
 };
 
-__device__ __forceinline__ void split_bf16(float v, __bf16 &h, __bf16 &l) {
-    h = (__bf16)v;
-    l = (__bf16)(v - (float)h);
-}
-
-// op(B)(k, n0 + lane % 16) of a K x N column-major FP32 operand, split
-__device__ __forceinline__ void small_loadB_split(SplitB &b, const float *Bp, int64_t ldb, int N, int K, int n0) {
+// op(B)(k, n0 + lane % 16) of a K x N column-major operand in split-BF16 words
+__device__ __forceinline__ void small_loadB_split(SplitB &b, const Pk32 *Bp, int64_t ldb, int N, int K, int n0) {
     const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
-    float v[2][8];
+    uint32_t v[2][8];
     if (!Bp || K <= 0) {
 #pragma unroll
         for (int c = 0; c < 2; c++)
 #pragma unroll
-            for (int e = 0; e < 8; e++) v[c][e] = 0.0f;
+            for (int e = 0; e < 8; e++) v[c][e] = 0;
     } else {
-        const SELINV_GLOBAL float *B = gptr(Bp);
+        const SELINV_GLOBAL uint32_t *B = gptr((const uint32_t *)Bp);
         const int n = n0 + li;
         const int64_t nc = min(n, N - 1);
 #pragma unroll
@@ -213,14 +209,14 @@ __device__ __forceinline__ void small_loadB_split(SplitB &b, const float *Bp, in
 #pragma unroll
         for (int c = 0; c < 2; c++)
 #pragma unroll
-            for (int e = 0; e < 8; e++) v[c][e] = (n < N && 32 * c + 8 * lk + e < K) ? v[c][e] : 0.0f;
+            for (int e = 0; e < 8; e++) v[c][e] = (n < N && 32 * c + 8 * lk + e < K) ? v[c][e] : 0;
     }
 #pragma unroll
     for (int c = 0; c < 2; c++)
 #pragma unroll
         for (int e = 0; e < 8; e++) {
             __bf16 h, l;
-            split_bf16(v[c][e], h, l);
+            split_bf16(Pk32{v[c][e]}, h, l);
             b.h[c][e] = h;
             b.l[c][e] = l;
         }
@@ -258,8 +254,8 @@ template <int MODE>
 struct SmallB {
     typedef typename Mode<MODE>::T T;
     T v[16];
-    __device__ __forceinline__ void load(const T *Bp, int64_t ldb, int N, int K, int n0) {
-        small_loadB<T>(v, Bp, ldb, N, K, n0);
+    __device__ __forceinline__ void load(const void *Bp, int64_t ldb, int N, int K, int n0) {
+        small_loadB<T>(v, (const T *)Bp, ldb, N, K, n0);
     }
     template <typename GetA>
     __device__ __forceinline__ typename SmallMfma<T>::Acc tile(GetA getA, int M, int K, int m0) const {
@@ -269,8 +265,8 @@ struct SmallB {
 template <>
 struct SmallB<CMP_BF16X3> {
     SplitB v;
-    __device__ __forceinline__ void load(const float *Bp, int64_t ldb, int N, int K, int n0) {
-        small_loadB_split(v, Bp, ldb, N, K, n0);
+    __device__ __forceinline__ void load(const void *Bp, int64_t ldb, int N, int K, int n0) {
+        small_loadB_split(v, (const Pk32 *)Bp, ldb, N, K, n0);
     }
     template <typename GetA>
     __device__ __forceinline__ v4f tile(GetA getA, int M, int K, int m0) const {
@@ -345,9 +341,9 @@ __global__ __launch_bounds__(256, 4) void small_kernel(const MatDev *__restrict_
     const GemmProb *pzl = it.pzl >= 0 ? &probs[it.pzl] : nullptr;
     const GemmProb *pg4 = it.pg4 >= 0 ? &probs[it.pg4] : nullptr;
     SmallB<MODE> bL, bU;
-    bL.load(pzu ? (const T *)pzu->B : nullptr, pzu ? pzu->ldb : 1, s, cl, n0);
+    bL.load(pzu ? pzu->B : nullptr, pzu ? pzu->ldb : 1, s, cl, n0);
     const GemmProb *pu = pzl ? pzl : pg4;  // Uhat: op(B) of steps 5 and 4
-    bU.load(pu ? (const T *)pu->B : nullptr, pu ? pu->ldb : 1, s, cu, n0);
+    bU.load(pu ? pu->B : nullptr, pu ? pu->ldb : 1, s, cu, n0);
 
     // (a small supernode with a non-empty G_K always has source codes)
     if (cl > 0 && cu > 0) gather_small_codes<T>(mats[it.mat], cl, cu, it.c_off, sm.g.tileS);

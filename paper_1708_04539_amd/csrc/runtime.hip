@@ -805,7 +805,7 @@ selinv_status build_sweep(std::vector<selinv_handle> &hs, const DevAlloc &al, in
                         t.Zd = b.Zd + r.off_d;
                         t.cl = r.cl;
                         t.cu = r.cu;
-                        t.f32out = e == 4;
+                        t.f32out = e == 8 ? 0 : mode_of(prec) == CMP_BF16X3 ? 2 : 1;
                         X.check(t.D, r.s, r.s, r.s, 8);
                         X.check(t.Zd, r.s, r.s, r.s, 8);
                         if (t.lpan) X.check(t.lpan, r.cl, r.s, r.cl, 8), X.check(t.Lh, r.cl, r.s, r.cl, e);
@@ -1147,7 +1147,8 @@ selinv_status build_sweep(std::vector<selinv_handle> &hs, const DevAlloc &al, in
                     X.check(P0, (int64_t)r.s * r.s, np, (int64_t)r.s * r.s, 8);
                     red_of[gid] = (int)reds.size();
                     reds.push_back(ReduceItem{b.Zd + r.off_d, P0, r.s, half ? r.s / 2 : r.s, r.s, np,
-                                              (int64_t)r.s * r.s, -1, -1, e == 4, half ? 1 : 0});
+                                              (int64_t)r.s * r.s, -1, -1,
+                                              e == 8 ? 0 : mode_of(prec) == CMP_BF16X3 ? 2 : 1, half ? 1 : 0});
                     S->red4_mn[d] = std::max<int64_t>(S->red4_mn[d], (int64_t)r.s * r.s);
                 }
             }
@@ -1450,7 +1451,7 @@ hipError_t launch_sweep(const Sweep &S, hipStream_t st, std::vector<hipEvent_t> 
         if ((e = launch_small(mode, S.d_mats, S.d_probs, S.d_small + S.small[d].off, S.small[d].count, st)))
             return e;
         mark(4 + 4 * d);
-        if ((e = launch_gather(f64, S.d_mats, S.d_gt + S.gat[d].off, S.gat[d].count, st))) return e;
+        if ((e = launch_gather(mode, S.d_mats, S.d_gt + S.gat[d].off, S.gat[d].count, st))) return e;
         mark(5 + 4 * d);
         if (S.vg[d]) {
             if ((e = launch_gemm_g35(mode, S.g35[d].tile, S.d_probs, S.d_tiles + S.g35[d].off, S.g35[d].count,

@@ -41,23 +41,64 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
+// A split-BF16 operand element: x as hi = bf16(x) in the upper half and lo =
+// bf16(x - hi) in the lower one, the pair the products take.
+struct Pk32 {
+    uint32_t w;
+};
+// The FP32 value of x as the compiler may not see through: it would fold the
+// two roundings x -> FP32 -> bf16 into one, at eight more FP64 and integer
+// instructions an element, and hi would not be that of the FP32 value.
+template <typename T>
+__device__ __forceinline__ float as_f32(T x) {
+    float f = (float)x;
+    if constexpr (sizeof(T) == sizeof(double)) asm("" : "+v"(f));
+    return f;
+}
+__device__ __forceinline__ void split_bf16(float v, __bf16 &h, __bf16 &l) {
+    h = (__bf16)v;
+    l = (__bf16)(v - (float)h);
+}
+__device__ __forceinline__ void split_bf16(Pk32 v, __bf16 &h, __bf16 &l) {
+    h = __builtin_bit_cast(__bf16, (uint16_t)(v.w >> 16));
+    l = __builtin_bit_cast(__bf16, (uint16_t)v.w);
+}
+// An element of storage type T as memory holds it, and v in that form
+template <typename T>
+using raw_t = std::conditional_t<std::is_same<T, Pk32>::value, uint32_t, T>;
+template <typename T>
+__device__ __forceinline__ raw_t<T> stored(double v) {
+    if constexpr (std::is_same<T, Pk32>::value) {
+        __bf16 h, l;
+        split_bf16(as_f32(v), h, l);
+        return (uint32_t)__builtin_bit_cast(uint16_t, h) << 16 | __builtin_bit_cast(uint16_t, l);
+    } else {
+        return (T)v;
+    }
+}
+
+// T: arithmetic and the A^{-T} panels; G: the arrays only the products read
+// (G_K and the normalised panels Lhat, Uhat).  Split-BF16 keeps those as Pk32:
+// each element is split once, where it is written, and not again by every tile
+// that reads it; the products see the same pair either way.
 template <int MODE>
 struct Mode;
 template <>
 struct Mode<CMP_F64> {
-    typedef double T;
+    typedef double T, G;
     typedef v4d Acc;
     static constexpr int BK = 16;
 };
 template <>
 struct Mode<CMP_F32> {
-    typedef float T;
+    typedef float T, G;
     typedef v4f Acc;
     static constexpr int BK = 16;
 };
 template <>
 struct Mode<CMP_BF16X3> {
     typedef float T;
+    typedef Pk32 G;
     typedef v4f Acc;
     static constexpr int BK = 32;
 };
@@ -94,6 +135,15 @@ struct Smem<CMP_BF16X3, BM, BN, BK> {
     __bf16 bh[2][BN][P], bl[2][BN][P];
 };
 
+// what split_bf16 takes of a loaded operand element
+template <typename T>
+__device__ __forceinline__ auto split_in(raw_t<T> x) {
+    if constexpr (std::is_same<T, Pk32>::value)
+        return Pk32{x};
+    else
+        return as_f32(x);
+}
+
 // An operand of the split-BF16 form that is contiguous along k (A with
 // op = T, B with op = N): each thread moves 4 consecutive k of R / 32 rows of
 // every 32-wide chunk, with one 16-byte load (two for FP64 operands) per row
@@ -102,12 +152,13 @@ struct Smem<CMP_BF16X3, BM, BN, BK> {
 template <int R, typename TA>
 struct SplitKRows {
     static constexpr int NT = R / 32;
-    typedef TA v4 __attribute__((ext_vector_type(4), aligned(sizeof(TA))));
+    typedef raw_t<TA> E;
+    typedef E v4 __attribute__((ext_vector_type(4), aligned(sizeof(E))));
     typedef __bf16 v4b __attribute__((ext_vector_type(4)));
     struct Regs {  // one chunk in flight
         v4 reg[NT];
     };
-    const SELINV_GLOBAL TA *ptr[NT];
+    const SELINV_GLOBAL E *ptr[NT];
     // Row of element t: the 8-lane groups of one 16-lane store phase take
     // rows 4 apart (group 8p + q -> row 8p + q / 2 + 4 (q & 1)), whose 64-byte
     // spans of the 80-byte padded rows fall on disjoint banks; consecutive
@@ -120,7 +171,7 @@ struct SplitKRows {
     __device__ __forceinline__ int kk() const { return 4 * (int)(threadIdx.x & 7); }
     // row r of the operand starts at base + r ld (rows clamped into [0, rows))
     __device__ __forceinline__ void init(const void *base, int64_t ld, int r0, int rows) {
-        const SELINV_GLOBAL TA *B = gptr((const TA *)base);
+        const SELINV_GLOBAL E *B = gptr((const E *)base);
 #pragma unroll
         for (int t = 0; t < NT; t++) ptr[t] = B + (int64_t)min(r0 + row(t), rows - 1) * ld + kk();
     }
@@ -145,10 +196,10 @@ struct SplitKRows {
             v4b h4, l4;
 #pragma unroll
             for (int e = 0; e < 4; e++) {
-                const float v = (r0 + row(t) < rows && k0 + kk() + e < K) ? (float)reg[t][e] : 0.0f;
-                const __bf16 h = (__bf16)v;
+                __bf16 h, l;
+                split_bf16(split_in<TA>(r0 + row(t) < rows && k0 + kk() + e < K ? reg[t][e] : (E)0), h, l);
                 h4[e] = h;
-                l4[e] = (__bf16)(v - (float)h);
+                l4[e] = l;
             }
             *(v4b *)&hi[row(t)][kk()] = h4;
             *(v4b *)&lo[row(t)][kk()] = l4;
@@ -171,9 +222,10 @@ template <int R, typename TA>
 struct SplitMRows {
     static constexpr int KB = R / 32;
     static constexpr int TPK = R / 4;  // threads along the rows
-    typedef TA v4 __attribute__((ext_vector_type(4), aligned(sizeof(TA))));
+    typedef raw_t<TA> E;
+    typedef E v4 __attribute__((ext_vector_type(4), aligned(sizeof(E))));
     typedef __bf16 vkb __attribute__((ext_vector_type(KB)));
-    const SELINV_GLOBAL TA *ptr;  // row r0 + r4 (0 when the quad is not whole) of k = kq
+    const SELINV_GLOBAL E *ptr;  // row r0 + r4 (0 when the quad is not whole) of k = kq
     int64_t ld;
     int r0, rows;
     bool full;  // all 4 rows of the quad inside the operand
@@ -201,7 +253,7 @@ struct SplitMRows {
         r0 = r0_;
         rows = rows_;
         full = r0 + r4() + 3 < rows;
-        ptr = gptr((const TA *)base) + (full ? r0 + r4() : 0) + (int64_t)kq() * ld;
+        ptr = gptr((const E *)base) + (full ? r0 + r4() : 0) + (int64_t)kq() * ld;
     }
     __device__ __forceinline__ void load(Regs &g, int k0, int K) const {
         v4(&reg)[KB] = g.reg;
@@ -227,10 +279,10 @@ struct SplitMRows {
             vkb h, l;
 #pragma unroll
             for (int e = 0; e < KB; e++) {
-                const float v = (r0 + r4() + q < rows && k0 + kq() + e < K) ? (float)reg[e][q] : 0.0f;
-                const __bf16 b = (__bf16)v;
+                __bf16 b, c;
+                split_bf16(split_in<TA>(r0 + r4() + q < rows && k0 + kq() + e < K ? reg[e][q] : (E)0), b, c);
                 h[e] = b;
-                l[e] = (__bf16)(v - (float)b);
+                l[e] = c;
             }
             const int r = r4() + q, kp = kq() ^ swz(r);
             *(vkb *)&hi[r][kp] = h;
@@ -250,8 +302,8 @@ __device__ __forceinline__ void gemm_store(const GemmProb &p, const int m0, cons
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int M = p.M, N = p.N;
-    SELINV_GLOBAL TC *__restrict__ C = gptr_w((TC *)p.C);
-    const SELINV_GLOBAL TC *__restrict__ Cin = gptr((const TC *)p.Cin);
+    SELINV_GLOBAL raw_t<TC> *__restrict__ C = gptr_w((raw_t<TC> *)p.C);
+    const SELINV_GLOBAL raw_t<TC> *__restrict__ Cin = gptr((const raw_t<TC> *)p.Cin);
     const int64_t ldc = p.ldc, ldcin = p.ldcin;
     const double alpha = p.alpha, beta = p.beta;
     // rows of the 16x16 result held by this lane: v_mfma_f64_16x16x4
@@ -296,8 +348,8 @@ __device__ __forceinline__ void gemm_store(const GemmProb &p, const int m0, cons
                     if (gn >= N) continue;
                     double r = alpha * (double)acc[i][j][v];
                     if (has_cin) r += beta * cin[ii][j][v];
-                    C[gm + (int64_t)gn * ldc] = (TC)r;
-                    if (p.cpx) C[(gm ^ 1) + (int64_t)gn * ldc + ldc / 2] = (TC)(csign * r);
+                    C[gm + (int64_t)gn * ldc] = stored<TC>(r);
+                    if (p.cpx) C[(gm ^ 1) + (int64_t)gn * ldc + ldc / 2] = stored<TC>(csign * r);
                     if constexpr (PUSH) acc[i][j][v] = (TC)r;  // the stored value, for the push below
                 }
         }
@@ -315,7 +367,7 @@ __device__ __forceinline__ void gemm_store(const GemmProb &p, const int m0, cons
                 const SELINV_GLOBAL int32_t *posL = gptr(Md.push_pos) + gptr(Md.push_off)[K];
                 const SELINV_GLOBAL int32_t *posU = posL + sP;
                 const int64_t clK = sn[K].cl;
-                SELINV_GLOBAL TG *G = gptr_w((TG *)Md.G) + sn[K].g_off;
+                SELINV_GLOBAL raw_t<TG> *G = gptr_w((raw_t<TG> *)Md.G) + sn[K].g_off;
 #pragma unroll
                 for (int i = 0; i < TM; i++) {
                     const int gm = m0 + wm * WM + i * 16 + (lane & 15);
@@ -324,7 +376,7 @@ __device__ __forceinline__ void gemm_store(const GemmProb &p, const int m0, cons
                     // complex blocks: column gn of the problem is column 2 gn
                     // of A^{-T}(P,P), and it gives entry (gm ^ 1, 2 gn + 1)
                     const int a1 = p.cpx ? posL[gm ^ 1] : -1;
-                    const TG csign = (gm & 1) ? (TG)-1 : (TG)1;
+                    const double csign = (gm & 1) ? -1.0 : 1.0;
 #pragma unroll
                     for (int j = 0; j < TN; j++)
 #pragma unroll
@@ -333,10 +385,10 @@ __device__ __forceinline__ void gemm_store(const GemmProb &p, const int m0, cons
                             if (gn >= N) continue;
                             const int c = p.cpx ? 2 * gn : gn;
                             const int b = posU[c];
-                            if (a >= 0 && b >= 0) G[a + b * clK] = (TG)acc[i][j][v];
+                            if (a >= 0 && b >= 0) G[a + b * clK] = stored<TG>(acc[i][j][v]);
                             if (p.cpx) {
                                 const int b1 = posU[c + 1];
-                                if (a1 >= 0 && b1 >= 0) G[a1 + b1 * clK] = csign * (TG)acc[i][j][v];
+                                if (a1 >= 0 && b1 >= 0) G[a1 + b1 * clK] = stored<TG>(csign * acc[i][j][v]);
                             }
                         }
                 }
@@ -364,8 +416,8 @@ __device__ __forceinline__ void gemm_store(const GemmProb &p, const int m0, cons
 // of chunk c, so that the values' addresses are in registers one chunk ahead
 // and the loop keeps one round trip per chunk in flight, as for a stored
 // operand.  The staged values equal those the gather would have stored.
-template <int MODE, int BM, int BN, typename TA, typename TC, bool CIN, int BK, int OPA, int OPB, bool PUSH,
-          typename TG, bool GA = false>
+template <int MODE, int BM, int BN, typename TA, typename TB, typename TC, bool CIN, int BK, int OPA, int OPB,
+          bool PUSH, bool GA = false>
 __device__ __forceinline__ void gemm_tile_op(const GemmProb &p, const int m0, const int n0,
                                              Smem<MODE, BM, BN, BK> &sm, const MatDev *mats) {
     typedef typename Mode<MODE>::T T;
@@ -394,17 +446,19 @@ __device__ __forceinline__ void gemm_tile_op(const GemmProb &p, const int m0, co
     // with op = N) or along the rows (A with op = N, B with op = T)
     constexpr bool VA = MODE == CMP_BF16X3 && !GA, VB = MODE == CMP_BF16X3;
     typedef std::conditional_t<OPA == 1, SplitKRows<BM, TA>, SplitMRows<BM, TA>> VecA;
-    typedef std::conditional_t<OPB == 0, SplitKRows<BN, TA>, SplitMRows<BN, TA>> VecB;
+    typedef std::conditional_t<OPB == 0, SplitKRows<BN, TB>, SplitMRows<BN, TB>> VecB;
     VecA va;
     VecB vb;
     if constexpr (VA) va.init(p.A, lda, m0, M);
     if constexpr (VB) vb.init(p.B, ldb, n0, N);
 
-    const SELINV_GLOBAL TA *pa[GA ? 1 : LA];
+    typedef raw_t<TA> EA;
+    typedef raw_t<TB> EB;
+    const SELINV_GLOBAL EA *pa[GA ? 1 : LA];
     const SELINV_GLOBAL uint32_t *pc[GA ? LA : 1];  // GA: codes of this thread's A elements
-    const SELINV_GLOBAL TA *pb[LB];
+    const SELINV_GLOBAL EB *pb[LB];
     {
-        const SELINV_GLOBAL TA *B = gptr((const TA *)p.B);
+        const SELINV_GLOBAL EB *B = gptr((const EB *)p.B);
         if constexpr (GA) {
             // G_K is c_L x c_U with ld = lda = c_L, laid out as a stored G would be
             const SELINV_GLOBAL uint32_t *Cd = gptr(mats[p.gmat].gcA) + p.gcode;
@@ -414,7 +468,7 @@ __device__ __forceinline__ void gemm_tile_op(const GemmProb &p, const int m0, co
                 pc[t] = Cd + (OPA == 0 ? r : r * lda) + ak(t) * ksa;
             }
         } else {
-            const SELINV_GLOBAL TA *A = gptr((const TA *)p.A);
+            const SELINV_GLOBAL EA *A = gptr((const EA *)p.A);
 #pragma unroll
             for (int t = 0; t < LA; t++) {
                 const int64_t r = min(m0 + ai(t), M - 1);
@@ -438,12 +492,12 @@ __device__ __forceinline__ void gemm_tile_op(const GemmProb &p, const int m0, co
     // GA: the source arrays of matrix gmat, and the code of every A element
     // of the next chunk to load
     const SELINV_GLOBAL double *gZd = nullptr;
-    const SELINV_GLOBAL TA *gZL = nullptr, *gZU = nullptr;
+    const SELINV_GLOBAL EA *gZL = nullptr, *gZU = nullptr;
     if constexpr (GA) {
         const MatDev &Md = mats[p.gmat];
         gZd = gptr(Md.Zd);
-        gZL = gptr((const TA *)Md.ZL);
-        gZU = gptr((const TA *)Md.ZU);
+        gZL = gptr((const EA *)Md.ZL);
+        gZU = gptr((const EA *)Md.ZU);
     }
     uint32_t code[GA ? LA : 1];
     auto cload = [&](int c) {
@@ -459,15 +513,15 @@ __device__ __forceinline__ void gemm_tile_op(const GemmProb &p, const int m0, co
     // value named by a code (array << 30 | offset; 1 Zd, 2 ZL, 3 ZU): in the
     // mixed forms a diagonal-block entry is rounded to TA as the gather
     // rounds it
-    auto gval = [&](uint32_t cd) -> TA {
+    auto gval = [&](uint32_t cd) -> EA {
         const uint32_t kd = cd >> GCODE_SHIFT, off = cd & GCODE_MASK;
         if constexpr (sizeof(TA) == sizeof(double)) {
-            const SELINV_GLOBAL TA *src = kd == 1 ? (const SELINV_GLOBAL TA *)gZd : kd == 3 ? gZU : gZL;
+            const SELINV_GLOBAL EA *src = kd == 1 ? (const SELINV_GLOBAL EA *)gZd : kd == 3 ? gZU : gZL;
             return src[off];
         } else {
             const double vd = gZd[kd == 1 ? off : 0];
-            const TA v = (kd == 3 ? gZU : gZL)[kd == 1 ? 0 : off];
-            return kd == 1 ? (TA)vd : v;
+            const EA v = (kd == 3 ? gZU : gZL)[kd == 1 ? 0 : off];
+            return kd == 1 ? (EA)as_f32(vd) : v;
         }
     };
 
@@ -479,7 +533,8 @@ __device__ __forceinline__ void gemm_tile_op(const GemmProb &p, const int m0, co
     // cost occupancy; measured: two slots on the 128-wide split-BF16
     // steps-3/5 tile left C4 at 15.9 ms).
     constexpr int PF = BM == 32 ? 2 : 1;
-    TA ra[PF][VA ? 1 : LA], rb[PF][VB ? 1 : LB];
+    EA ra[PF][VA ? 1 : LA];
+    EB rb[PF][VB ? 1 : LB];
     typename VecA::Regs rva[PF];
     typename VecB::Regs rvb[PF];
     // chunk c into slot S
@@ -665,26 +720,25 @@ __device__ __forceinline__ void gemm_tile_op(const GemmProb &p, const int m0, co
         }
     }
 
-    gemm_store<MODE, BM, BN, TC, CIN, PUSH, TG>(p, m0, n0, acc, mats);
+    gemm_store<MODE, BM, BN, TC, CIN, PUSH, typename Mode<MODE>::G>(p, m0, n0, acc, mats);
 }
 
 // Dispatch on the operand forms of the problem (uniform across the
 // workgroup).
-template <int MODE, int BM, int BN, typename TA, typename TC, bool CIN, bool PUSH = false,
+template <int MODE, int BM, int BN, typename TA, typename TB, typename TC, bool CIN, bool PUSH = false,
           int BK = ChunkK<MODE, BM>::value>
 __device__ __forceinline__ void gemm_tile(const GemmProb &p, const int m0, const int n0,
                                           Smem<MODE, BM, BN, BK> &sm, const MatDev *mats = nullptr) {
-    typedef typename Mode<MODE>::T TG;
     if (p.opA == 0) {
         if (p.opB == 0)
-            gemm_tile_op<MODE, BM, BN, TA, TC, CIN, BK, 0, 0, PUSH, TG>(p, m0, n0, sm, mats);
+            gemm_tile_op<MODE, BM, BN, TA, TB, TC, CIN, BK, 0, 0, PUSH>(p, m0, n0, sm, mats);
         else
-            gemm_tile_op<MODE, BM, BN, TA, TC, CIN, BK, 0, 1, PUSH, TG>(p, m0, n0, sm, mats);
+            gemm_tile_op<MODE, BM, BN, TA, TB, TC, CIN, BK, 0, 1, PUSH>(p, m0, n0, sm, mats);
     } else {
         if (p.opB == 0)
-            gemm_tile_op<MODE, BM, BN, TA, TC, CIN, BK, 1, 0, PUSH, TG>(p, m0, n0, sm, mats);
+            gemm_tile_op<MODE, BM, BN, TA, TB, TC, CIN, BK, 1, 0, PUSH>(p, m0, n0, sm, mats);
         else
-            gemm_tile_op<MODE, BM, BN, TA, TC, CIN, BK, 1, 1, PUSH, TG>(p, m0, n0, sm, mats);
+            gemm_tile_op<MODE, BM, BN, TA, TB, TC, CIN, BK, 1, 1, PUSH>(p, m0, n0, sm, mats);
     }
 }
 
@@ -693,10 +747,11 @@ __device__ __forceinline__ void gemm_tile(const GemmProb &p, const int m0, const
 template <int MODE, int BM, int BN, typename TA, int BK = ChunkK<MODE, BM>::value>
 __device__ __forceinline__ void gemm_tile_g35(const GemmProb &p, const int m0, const int n0,
                                               Smem<MODE, BM, BN, BK> &sm, const MatDev *mats) {
+    typedef typename Mode<MODE>::G TB;
     if (p.opA == 0)
-        gemm_tile_op<MODE, BM, BN, TA, TA, false, BK, 0, 0, false, TA, true>(p, m0, n0, sm, mats);
+        gemm_tile_op<MODE, BM, BN, TA, TB, TA, false, BK, 0, 0, false, true>(p, m0, n0, sm, mats);
     else
-        gemm_tile_op<MODE, BM, BN, TA, TA, false, BK, 1, 0, false, TA, true>(p, m0, n0, sm, mats);
+        gemm_tile_op<MODE, BM, BN, TA, TB, TA, false, BK, 1, 0, false, true>(p, m0, n0, sm, mats);
 }
 
 // ---------------------------------------------------------------------------
@@ -746,6 +801,11 @@ typedef __attribute__((address_space(3))) char lds_char;
 template <typename T, int R, bool KC>
 struct DmaOperand {
     static constexpr int E = sizeof(T), BK = 128 / E, NI = R / 32, RB = R * E;
+    // row-contiguous layout: swizzle of row k (a lane reads k = lane / 16 of 4
+    // at a time, or 8 consecutive k of its quarter of 32)
+    static __device__ __forceinline__ int swz(int k) {
+        return ((std::is_same<T, Pk32>::value ? k >> 3 : k) & 3) * 16 * E & (RB - 1);
+    }
     const char *base;   // r0, k = 0
     int64_t size;       // bytes from base to the operand's end, and to the end of its last 16-byte unit
     int64_t kstep;      // bytes per chunk
@@ -771,7 +831,7 @@ struct DmaOperand {
                 voff[i] = (uint32_t)(min(r, lim) - first) * (uint32_t)rstep + u * 16;
             } else {
                 const int pos = lane * 16, k = q * PER + pos / RB;
-                voff[i] = (uint32_t)(k - first) * (uint32_t)rstep + ((pos % RB) ^ (((k & 3) * 16 * E) & (RB - 1)));
+                voff[i] = (uint32_t)(k - first) * (uint32_t)rstep + ((pos % RB) ^ swz(k));
             }
         }
     }
@@ -804,7 +864,7 @@ struct DmaOperand {
         if constexpr (KC)
             return r * 128 + (((k * E) / 16) ^ ((r >> 1) & 7)) * 16 + (k * E) % 16;
         else
-            return k * RB + ((r * E) ^ (((k & 3) * 16 * E) & (RB - 1)));
+            return k * RB + ((r * E) ^ swz(k));
     }
 };
 
@@ -824,10 +884,10 @@ template <int MODE, int BM, int BN, int ST, int OPA, int OPB>
 struct DmaProduct {
     static __device__ __forceinline__ void form(const GemmProb &p, const int m0, const int n0,
                                                 DmaSmem<BM, BN, ST> &sm, AccTile<MODE, BM, BN> &t) {
-        typedef typename Mode<MODE>::T T;
+        typedef typename Mode<MODE>::G T;
         typedef typename Mode<MODE>::Acc Acc;
+        constexpr bool PK = MODE == CMP_BF16X3;
         auto &acc = t.a;
-        static_assert(MODE == CMP_F64 || MODE == CMP_F32, "operands in the arithmetic's own type");
         static_assert(ST == 2 || ST == 3, "stages");
         typedef DmaOperand<T, BM, OPA == 1> OA;
         typedef DmaOperand<T, BN, OPB == 0> OB;
@@ -851,34 +911,86 @@ struct DmaProduct {
             for (int j = 0; j < TN; j++) acc[i][j] = Acc{0, 0, 0, 0};
         // LDS offsets of this lane's operands (stage 0): of 16-row tile i at k
         // step kk.  k-contiguous: the unit depends on kk, the tile is a constant
-        // further on; row-contiguous: the other way round.
-        constexpr int KS = BK / 4;
-        int oa[OPA == 1 ? KS : TM], ob[OPB == 0 ? KS : TN];
+        // further on; row-contiguous: the other way round.  Split-BF16: one
+        // step of 32, of which a lane takes 8 consecutive k, in two units or
+        // from 8 rows.
+        constexpr int KS = PK ? 1 : BK / 4, NU = PK ? 2 : KS;
+        int oa[OPA == 1 ? NU : TM], ob[OPB == 0 ? NU : TN];
 #pragma unroll
-        for (int q = 0; q < (OPA == 1 ? KS : TM); q++)
-            oa[q] = OPA == 1 ? OA::at(wm * WM + li, 4 * q + lk) : OA::at(wm * WM + 16 * q + li, lk);
+        for (int q = 0; q < (OPA == 1 ? NU : TM); q++)
+            oa[q] = OPA == 1 ? OA::at(wm * WM + li, PK ? 8 * lk + 4 * q : 4 * q + lk)
+                             : OA::at(wm * WM + 16 * q + li, PK ? 8 * lk : lk);
 #pragma unroll
-        for (int q = 0; q < (OPB == 0 ? KS : TN); q++)
-            ob[q] = BM * 128 + (OPB == 0 ? OB::at(wn * WN + li, 4 * q + lk) : OB::at(wn * WN + 16 * q + li, lk));
+        for (int q = 0; q < (OPB == 0 ? NU : TN); q++)
+            ob[q] = BM * 128 + (OPB == 0 ? OB::at(wn * WN + li, PK ? 8 * lk + 4 * q : 4 * q + lk)
+                                         : OB::at(wn * WN + 16 * q + li, PK ? 8 * lk : lk));
         auto kstep = [&](int st, int q) {
-            T av[TM], bv[TN];
+            if constexpr (PK) {
+                typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+                // tile i of an operand: the words of 8 k, parted into hi and lo
+                auto frag = [&](auto KC_, const auto &o, int i, int rb, v8bf &hi, v8bf &lo) {
+                    constexpr bool KC = decltype(KC_)::value;
+                    uint32_t w[8];
+                    if constexpr (KC) {
 #pragma unroll
-            for (int i = 0; i < TM; i++)
-                av[i] = *(const __attribute__((address_space(3))) T *)(lds + (OPA == 1 ? oa[q] : oa[i]) +
-                                                                       (st * SB + (OPA == 1 ? i * 16 * 128 : 4 * q * OA::RB)));
+                        for (int u = 0; u < 2; u++) {
+                            const v4u x = *(const __attribute__((address_space(3))) v4u *)(lds + o[u] +
+                                                                                          (st * SB + i * 16 * 128));
 #pragma unroll
-            for (int j = 0; j < TN; j++)
-                bv[j] = *(const __attribute__((address_space(3))) T *)(lds + (OPB == 0 ? ob[q] : ob[j]) +
-                                                                       (st * SB + (OPB == 0 ? j * 16 * 128 : 4 * q * OB::RB)));
+                            for (int e = 0; e < 4; e++) w[4 * u + e] = x[e];
+                        }
+                    } else {
 #pragma unroll
-            for (int i = 0; i < TM; i++)
+                        for (int e = 0; e < 8; e++)
+                            w[e] = *(const __attribute__((address_space(3))) uint32_t *)(lds + o[i] +
+                                                                                         (st * SB + e * rb));
+                    }
+                    v4u h, l;
 #pragma unroll
-                for (int j = 0; j < TN; j++) {
-                    if constexpr (MODE == CMP_F64)
-                        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(bv[j], av[i], acc[i][j], 0, 0, 0);
-                    else
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[j], av[i], acc[i][j], 0, 0, 0);
+                    for (int e = 0; e < 4; e++) {
+                        h[e] = __builtin_amdgcn_perm(w[2 * e + 1], w[2 * e], 0x07060302);
+                        l[e] = __builtin_amdgcn_perm(w[2 * e + 1], w[2 * e], 0x05040100);
+                    }
+                    hi = __builtin_bit_cast(v8bf, h);
+                    lo = __builtin_bit_cast(v8bf, l);
+                };
+                v8bf bh[TN], bl[TN];
+#pragma unroll
+                for (int j = 0; j < TN; j++)
+                    frag(std::integral_constant<bool, OPB == 0>{}, ob, j, OB::RB, bh[j], bl[j]);
+#pragma unroll
+                for (int i = 0; i < TM; i++) {
+                    v8bf ah, al;
+                    frag(std::integral_constant<bool, OPA == 1>{}, oa, i, OA::RB, ah, al);
+#pragma unroll
+                    for (int j = 0; j < TN; j++) {
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl[j], ah, acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], al, acc[i][j], 0, 0, 0);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], ah, acc[i][j], 0, 0, 0);
+                    }
                 }
+            } else {
+                T av[TM], bv[TN];
+#pragma unroll
+                for (int i = 0; i < TM; i++)
+                    av[i] = *(const __attribute__((address_space(3))) T *)(lds + (OPA == 1 ? oa[q] : oa[i]) +
+                                                                           (st * SB +
+                                                                            (OPA == 1 ? i * 16 * 128 : 4 * q * OA::RB)));
+#pragma unroll
+                for (int j = 0; j < TN; j++)
+                    bv[j] = *(const __attribute__((address_space(3))) T *)(lds + (OPB == 0 ? ob[q] : ob[j]) +
+                                                                           (st * SB +
+                                                                            (OPB == 0 ? j * 16 * 128 : 4 * q * OB::RB)));
+#pragma unroll
+                for (int i = 0; i < TM; i++)
+#pragma unroll
+                    for (int j = 0; j < TN; j++) {
+                        if constexpr (MODE == CMP_F64)
+                            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(bv[j], av[i], acc[i][j], 0, 0, 0);
+                        else
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[j], av[i], acc[i][j], 0, 0, 0);
+                    }
+            }
         };
         // chunks whose products are all zero by the operands' triangular
         // structure are skipped, as in gemm_tile_op
@@ -917,42 +1029,42 @@ struct DmaProduct {
             // last, partial chunk
             const int S = max(nfull - c0, 0) % ST;
             arrive(nch - 1, S);
-            const int kr = K - nfull * BK, nz = (4 - (kr & 3)) & 3;
+            constexpr int KM = PK ? BK : 4;  // k of one MFMA
+            const int kr = K - nfull * BK, nz = (KM - kr % KM) % KM;
             for (int e = threadIdx.x; e < nz * (BM + BN); e += 256) {
                 const int k = kr + e / (BM + BN), r = e % (BM + BN);
                 const int o = r < BM ? OA::at(r, k) : BM * 128 + OB::at(r - BM, k);
-                *(__attribute__((address_space(3))) T *)(lds + S * SB + o) = (T)0;
+                *(__attribute__((address_space(3))) raw_t<T> *)(lds + S * SB + o) = 0;
             }
             dma_barrier<0>();
 #pragma unroll
             for (int q = 0; q < KS; q++)
-                if (4 * q < kr) kstep(S, q);
+                if (KM * q < kr) kstep(S, q);
         }
     }
 };
 
-template <int MODE, int BM, int BN, int ST, typename TC, bool CIN, int OPA, int OPB, bool PUSH, typename TG>
+template <int MODE, int BM, int BN, int ST, typename TC, bool CIN, int OPA, int OPB, bool PUSH>
 __device__ __forceinline__ void gemm_tile_dma_op(const GemmProb &p, const int m0, const int n0,
                                                  DmaSmem<BM, BN, ST> &sm, const MatDev *mats) {
     AccTile<MODE, BM, BN> t;
     DmaProduct<MODE, BM, BN, ST, OPA, OPB>::form(p, m0, n0, sm, t);
-    gemm_store<MODE, BM, BN, TC, CIN, PUSH, TG>(p, m0, n0, t.a, mats);
+    gemm_store<MODE, BM, BN, TC, CIN, PUSH, typename Mode<MODE>::G>(p, m0, n0, t.a, mats);
 }
 
 template <int MODE, int BM, int BN, int ST, typename TC, bool CIN, bool PUSH = false>
 __device__ __forceinline__ void gemm_tile_dma(const GemmProb &p, const int m0, const int n0, DmaSmem<BM, BN, ST> &sm,
                                               const MatDev *mats = nullptr) {
-    typedef typename Mode<MODE>::T TG;
     if (p.opA == 0) {
         if (p.opB == 0)
-            gemm_tile_dma_op<MODE, BM, BN, ST, TC, CIN, 0, 0, PUSH, TG>(p, m0, n0, sm, mats);
+            gemm_tile_dma_op<MODE, BM, BN, ST, TC, CIN, 0, 0, PUSH>(p, m0, n0, sm, mats);
         else
-            gemm_tile_dma_op<MODE, BM, BN, ST, TC, CIN, 0, 1, PUSH, TG>(p, m0, n0, sm, mats);
+            gemm_tile_dma_op<MODE, BM, BN, ST, TC, CIN, 0, 1, PUSH>(p, m0, n0, sm, mats);
     } else {
         if (p.opB == 0)
-            gemm_tile_dma_op<MODE, BM, BN, ST, TC, CIN, 1, 0, PUSH, TG>(p, m0, n0, sm, mats);
+            gemm_tile_dma_op<MODE, BM, BN, ST, TC, CIN, 1, 0, PUSH>(p, m0, n0, sm, mats);
         else
-            gemm_tile_dma_op<MODE, BM, BN, ST, TC, CIN, 1, 1, PUSH, TG>(p, m0, n0, sm, mats);
+            gemm_tile_dma_op<MODE, BM, BN, ST, TC, CIN, 1, 1, PUSH>(p, m0, n0, sm, mats);
     }
 }
 
@@ -991,7 +1103,7 @@ __device__ __forceinline__ GatherTile gather_desc(const MatDev &M, int mat, int 
 // kernels that share this code stays unchanged).  Diagonal-block and L-side
 // entries are read with the threads along the rows of G (contiguous in ZL),
 // U-side entries with the threads along its columns (contiguous in ZU).
-template <typename T, bool STORE>
+template <typename T, typename TG, bool STORE>
 __device__ __forceinline__ void gather_tile_codes(const MatDev &M, const GatherTile &gt, GatherSmem<T> &sm) {
     T(&tileS)[64][65] = sm.tileS;
     constexpr int CH = 8;
@@ -1046,11 +1158,11 @@ __device__ __forceinline__ void gather_tile_codes(const MatDev &M, const GatherT
     }
     __syncthreads();
     if constexpr (!STORE) return;
-    SELINV_GLOBAL T *G = gptr_w((T *)M.G + gt.g_off);
+    SELINV_GLOBAL raw_t<TG> *G = gptr_w((raw_t<TG> *)M.G + gt.g_off);
 #pragma unroll
     for (int t = 0; t < 2 * CH; t++) {
         const int e = tid + 256 * t, ia = e & 63, ib = e >> 6;
-        if (keep >> t & 1) G[(a0 + ia) + (int64_t)(b0 + ib) * cl] = tileS[ib][ia];
+        if (keep >> t & 1) G[(a0 + ia) + (int64_t)(b0 + ib) * cl] = stored<TG>(tileS[ib][ia]);
     }
 }
 
@@ -1062,10 +1174,11 @@ __device__ __forceinline__ void gather_tile_codes(const MatDev &M, const GatherT
 // (gt.c_off >= 0) the codes name the sources; otherwise the relative-index
 // maps do.
 // STORE = false leaves the tile in LDS only (sm.tileS[b][a] = G(a0+a, b0+b)).
-template <typename T, bool STORE = true>
+// TG: the type G_K is stored in.
+template <typename T, typename TG, bool STORE = true>
 __device__ __forceinline__ void gather_tile(const MatDev &M, const GatherTile &gt, GatherSmem<T> &sm) {
     if (gt.c_off >= 0) {
-        gather_tile_codes<T, STORE>(M, gt, sm);
+        gather_tile_codes<T, TG, STORE>(M, gt, sm);
         return;
     }
     const int a0 = gt.a0, b0 = gt.b0, skip = gt.skip;
@@ -1189,12 +1302,12 @@ __device__ __forceinline__ void gather_tile(const MatDev &M, const GatherTile &g
     }
     __syncthreads();
     if constexpr (!STORE) return;
-    SELINV_GLOBAL T *G = gptr_w((T *)M.G + sk_g_off);
+    SELINV_GLOBAL raw_t<TG> *G = gptr_w((raw_t<TG> *)M.G + sk_g_off);
     for (int e = tid; e < 64 * 64; e += 256) {
         const int ia = e & 63, ib = e >> 6;
         // entries of the skipped diagonal block are written by its owner
         if (ia < na && ib < nb && !(rowI[ia] == skip && colJ[ib] == skip))
-            G[(a0 + ia) + (int64_t)(b0 + ib) * sk_cl] = tileS[ib][ia];
+            G[(a0 + ia) + (int64_t)(b0 + ib) * sk_cl] = stored<TG>(tileS[ib][ia]);
     }
 }
 
