@@ -63,10 +63,17 @@ struct MatDev {
 // loads without reading the supernode record first.
 struct GatherTile {
     int32_t mat, K, a0, b0;
-    int32_t skip, cl, cu, pad;
+    // kind != 0: all rows of the tile in one supernode I, all columns in one
+    // supernode J, so that every entry comes from the same block: 1 the
+    // diagonal block (I = J), 2 the L panel of J (I > J), 3 the U panel of I
+    // (I < J)
+    int32_t skip, cl, cu, kind;
     int64_t g_off, c_off;       // as in SnRec
     int64_t skip_lo, skip_hi;   // elements of Zd holding the skipped diagonal block
     int64_t rl_off, ru_off;     // as in SnRec
+    // kind 2: where mapL has the positions of the tile's rows in R_L(J); kind
+    // 3: where mapU has those of its columns in R_U(I)
+    int64_t m_off;
 };
 
 // C = alpha * op(A) op(B) + beta * Cin, column-major, op = N (0) or T (1)

@@ -57,10 +57,7 @@ __global__ __launch_bounds__(256) void scatter_values_kernel(const int64_t *__re
 // columns each (lane = column, substitution with the panel's unit L), then all
 // four update the rest on v_mfma_f64_16x16x4.
 __device__ __forceinline__ double lane_value(double v, int lane) {
-    const int64_t b = __builtin_bit_cast(int64_t, v);
-    const uint32_t lo = __builtin_amdgcn_readlane((int)b, lane);
-    const uint32_t hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-    return __builtin_bit_cast(double, (int64_t)(((uint64_t)hi << 32) | lo));
+    return __builtin_bit_cast(double, lane_value(__builtin_bit_cast(int64_t, v), lane));
 }
 
 template <class SM>

@@ -1186,8 +1186,12 @@ selinv_status build_sweep(std::vector<selinv_handle> &hs, const DevAlloc &al, in
                         }
                     }
                     for (int b0 = 0; b0 < r.cu; b0 += 64)
-                        for (int a0 = 0; a0 < r.cl; a0 += 64)
-                            gts.push_back(gather_tile_of(h, (int32_t)mi, K, a0, b0, skip));
+                        for (int a0 = 0; a0 < r.cl; a0 += 64) {
+                            const GatherTile g = gather_tile_of(h, (int32_t)mi, K, a0, b0, skip);
+                            // (a tile inside the parent's diagonal block is all its push)
+                            if (g.kind == 1 && h->P.supof[h->P.rl[h->P.rl_ptr[K] + a0]] == skip) continue;
+                            gts.push_back(g);
+                        }
                 }
             }
         }
@@ -1671,7 +1675,6 @@ GatherTile gather_tile_of(selinv_handle h, int32_t mi, int32_t K, int a0, int b0
     g.skip = skip;
     g.cl = r.cl;
     g.cu = r.cu;
-    g.pad = 0;
     g.g_off = r.g_off;
     g.c_off = r.c_off;
     g.skip_lo = g.skip_hi = 0;
@@ -1680,6 +1683,17 @@ GatherTile gather_tile_of(selinv_handle h, int32_t mi, int32_t K, int a0, int b0
     if (skip >= 0) {
         g.skip_lo = h->sn[skip].off_d;
         g.skip_hi = g.skip_lo + (int64_t)h->sn[skip].s * h->sn[skip].s;
+    }
+    // both index sets are sorted: one supernode if the first and last entries share it
+    const Plan &P = h->P;
+    const int64_t ra = P.rl_ptr[K] + a0, cb = P.ru_ptr[K] + b0;
+    const int32_t I = P.supof[P.rl[ra]], J = P.supof[P.ru[cb]];
+    g.kind = 0;
+    g.m_off = 0;
+    if (P.supof[P.rl[ra + std::min(64, r.cl - a0) - 1]] == I && P.supof[P.ru[cb + std::min(64, r.cu - b0) - 1]] == J) {
+        g.kind = I == J ? 1 : I > J ? 2 : 3;
+        if (g.kind == 2) g.m_off = P.l_coloff[cb] + a0;
+        if (g.kind == 3) g.m_off = P.u_rowoff[ra] + b0;
     }
     return g;
 }
@@ -2073,7 +2087,7 @@ static selinv_status build_lu(selinv_handle h) {
             const int cl = r.cl, cu = r.cu;
             if (cl == 0 || cu == 0) continue;
             for (int a0 = 0; a0 < cl; a0 += 64)
-                for (int b0 = 0; b0 < cu; b0 += 64) scs.push_back(GatherTile{0, K, a0, b0, -1, cl, cu, 0, 0, -1, 0, 0, 0, 0});
+                for (int b0 = 0; b0 < cu; b0 += 64) scs.push_back(GatherTile{0, K, a0, b0, -1, cl, cu, 0, 0, -1, 0, 0, 0, 0, 0});
             // destinations of every entry of W_K
             const int32_t *RL = P.rl.data() + P.rl_ptr[K], *RU = P.ru.data() + P.ru_ptr[K];
             for (int b2 = 0; b2 < cu && ok; b2++) {

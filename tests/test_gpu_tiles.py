@@ -172,3 +172,37 @@ def test_policy_in_place_levels(dims, cap, budget, prec):
     assert not any(s.level_stats(d)["gather_fused"] == 2 for d in range(L))
     _, _, y = s.export(sort=False)
     assert np.array_equal(x, y)
+
+
+# 64x64 gather tiles whose rows share one supernode and whose columns share
+# one (all three blocks they can come from, full and ragged) beside those that
+# straddle supernodes: read through the maps, the source codes, and against
+# the oracle
+@pytest.mark.parametrize("n,density,cap", [(400, 0.01, 64), (400, 0.01, 65), (400, 0.01, 130), (330, 0.7, 64),
+                                           (330, 0.7, 63), (330, 0.7, 129), (449, 0.004, 200)])
+@pytest.mark.parametrize("prec", ["fp64", "mixed_fp32", "mixed_bf16x3"])
+def test_gather_tiles_of_one_supernode(n, density, cap, prec):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_1708_04539_amd import selinv as si
+    print("[case] gather tiles", n, density, cap, prec, flush=True)
+    cp, ri, v, _ = random_sparse(n, density, 5)
+    o = Oracle(n, cp, ri, None, cap, 0, 0, 100).factor(v).selinv()
+    r2, c2, ref = o.export()
+    got = []
+    for budget in (0, -1):
+        s = si.SelInv(n, cp, ri, None, cap, 0, 100)
+        s.set_gather_code_budget(budget)
+        s.factor(v)
+        for form in ("stored", "auto"):
+            s.set_gather_form(form)
+            s.run(prec)
+            r, c, x = s.export(sort=False)
+            got.append(x)
+        s.close()
+    k = np.lexsort((r, c))
+    assert np.array_equal(r[k], r2) and np.array_equal(c[k], c2)
+    assert np.abs(got[0][k] - ref).max() / np.abs(ref).max() <= TOL[prec]
+    for x in got[1:]:
+        assert np.array_equal(x, got[0])
