@@ -104,14 +104,22 @@ __global__ __launch_bounds__(256) void sweep_kernel(const PersistArgs a) {
 // Algorithm 1 steps 3-5 for one supernode, so that a level of them costs one
 // launch instead of three.
 //   0. each wavefront owns one block of 16 columns (of the s columns of the
-//      three results) and loads its columns of Lhat and Uhat straight from
-//      global memory into registers, before anything else: those loads are
-//      in flight during the gather;
+//      three results) and loads its columns of Lhat straight from global
+//      memory into registers, before anything else, those of Uhat after the
+//      gather's last loads;
 //   1. gather G_K (one tile) into LDS; it never goes to global memory;
 //   2. the step-3 product -G^T Lhat and the step-5 product -G Uhat^T, 16x16
 //      output tiles, op(A) from the LDS copy of G; the step-3 result is also
 //      kept in LDS;
 //   3. the step-4 product from that LDS copy and the Uhat registers.
+// Bound by round trips (item, descriptors, codes, values, operands) where a
+// level has few items, by the operands' scattered 32-byte pieces and the MFMA
+// chains where it fills the chip.  Hence: codes of the next gather round in
+// flight with the values of this one, Uhat and the initial A^{-T}(K,K) loaded
+// while earlier phases run, no loads past K, LDS reads without conditions (one
+// branch and wait per MFMA before).  256 / 512 / 1024 items of a 256x256 grid,
+// FP64: 18 / 15 / 26 us (20 / 17 / 34 before); 12 small systems at once 152
+// (179), 193x117 in FP32 43 (46).
 // When s < 49 several wavefronts share a column block and split its row
 // blocks.  Products run with the k order, operand roles and operand split of
 // the grouped GEMM (v_mfma_f64/f32_16x16x4; split-BF16: per 32-wide k chunk
@@ -158,26 +166,35 @@ __device__ __forceinline__ void small_loadB(T (&bv)[16], const T *Bp, int64_t ld
     const int n = n0 + li;
     const int64_t nc = min(n, N - 1);
 #pragma unroll
-    for (int q = 0; q < 16; q++) bv[q] = B[min(4 * q + lk, K - 1) + nc * ldb];
+    for (int q = 0; q < 16; q++) {
+        if (4 * (q & ~3) < K)  // (nothing is loaded for whole blocks of 16 k past K)
+            bv[q] = B[min(4 * q + lk, K - 1) + nc * ldb];
+        else
+            bv[q] = (T)0;
+    }
 #pragma unroll
     for (int q = 0; q < 16; q++) bv[q] = (n < N && 4 * q + lk < K) ? bv[q] : (T)0;
 }
 
 // One 16x16 tile (rows m0..) of op(A) op(B): op(A)(m, k) from getA (LDS),
-// op(B) from the registers of small_loadB, k < K <= 64.
+// op(B) from the registers of small_loadB, k < K <= 64, 16 k at a time: the LDS
+// tile is zero past its operand and op(B) past K, so the reads carry no
+// condition (each one of its own was a branch and an LDS wait per MFMA).
 template <typename T, typename GetA>
-__device__ __forceinline__ typename SmallMfma<T>::Acc small_tile(GetA getA, const T (&bv)[16], int M, int K,
-                                                                 int m0) {
+__device__ __forceinline__ typename SmallMfma<T>::Acc small_tile(GetA getA, const T (&bv)[16], int K, int m0) {
     typedef typename SmallMfma<T>::Acc Acc;
     const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
     Acc acc = {0, 0, 0, 0};
-    const int m = m0 + li;
 #pragma unroll
-    for (int q = 0; q < 16; q++) {
+    for (int q = 0; q < 16; q += 4) {
         if (4 * q >= K) break;
-        const int k = 4 * q + lk;
-        const T a = (m < M && k < K) ? getA(m, k) : (T)0;
-        acc = SmallMfma<T>::step(bv[q], a, acc);
+        T a[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) a[e] = getA(m0 + li, 4 * (q + e) + lk);
+        acc = SmallMfma<T>::step(bv[q], a[0], acc);
+#pragma unroll
+        for (int e = 1; e < 4; e++)
+            if (4 * (q + e) < K) acc = SmallMfma<T>::step(bv[q + e], a[e], acc);
     }
     return acc;
 }
@@ -205,7 +222,12 @@ __device__ __forceinline__ void small_loadB_split(SplitB &b, const Pk32 *Bp, int
 #pragma unroll
         for (int c = 0; c < 2; c++)
 #pragma unroll
-            for (int e = 0; e < 8; e++) v[c][e] = B[min(32 * c + 8 * lk + e, K - 1) + nc * ldb];
+            for (int e = 0; e < 8; e++) {
+                if (32 * c < K)
+                    v[c][e] = B[min(32 * c + 8 * lk + e, K - 1) + nc * ldb];
+                else
+                    v[c][e] = 0;
+            }
 #pragma unroll
         for (int c = 0; c < 2; c++)
 #pragma unroll
@@ -225,7 +247,7 @@ __device__ __forceinline__ void small_loadB_split(SplitB &b, const Pk32 *Bp, int
 // One 16x16 tile (rows m0..) of op(A) op(B) in split-BF16: op(A)(m, k) from
 // getA (LDS), op(B) split in registers, k < K <= 64.
 template <typename GetA>
-__device__ __forceinline__ v4f small_tile_split(GetA getA, const SplitB &b, int M, int K, int m0) {
+__device__ __forceinline__ v4f small_tile_split(GetA getA, const SplitB &b, int K, int m0) {
     const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
     v4f acc = {0, 0, 0, 0};
     const int m = m0 + li;
@@ -235,10 +257,8 @@ __device__ __forceinline__ v4f small_tile_split(GetA getA, const SplitB &b, int 
         v8bf ah, al;
 #pragma unroll
         for (int e = 0; e < 8; e++) {
-            const int k = 32 * c + 8 * lk + e;
-            const float a = (m < M && k < K) ? getA(m, k) : 0.0f;
             __bf16 h, l;
-            split_bf16(a, h, l);
+            split_bf16(getA(m, 32 * c + 8 * lk + e), h, l);
             ah[e] = h;
             al[e] = l;
         }
@@ -258,8 +278,8 @@ struct SmallB {
         small_loadB<T>(v, (const T *)Bp, ldb, N, K, n0);
     }
     template <typename GetA>
-    __device__ __forceinline__ typename SmallMfma<T>::Acc tile(GetA getA, int M, int K, int m0) const {
-        return small_tile<T>(getA, v, M, K, m0);
+    __device__ __forceinline__ typename SmallMfma<T>::Acc tile(GetA getA, int K, int m0) const {
+        return small_tile<T>(getA, v, K, m0);
     }
 };
 template <>
@@ -269,17 +289,21 @@ struct SmallB<CMP_BF16X3> {
         small_loadB_split(v, (const Pk32 *)Bp, ldb, N, K, n0);
     }
     template <typename GetA>
-    __device__ __forceinline__ v4f tile(GetA getA, int M, int K, int m0) const {
-        return small_tile_split(getA, v, M, K, m0);
+    __device__ __forceinline__ v4f tile(GetA getA, int K, int m0) const {
+        return small_tile_split(getA, v, K, m0);
     }
 };
+
+// e / c for 0 <= e < 64 c, c <= 64, from ic = 1 / c: (e + 1/2) / c lies at least
+// 1 / 128 from every integer, the two roundings move it by less than 64 * 2^-22.
+__device__ __forceinline__ int small_div(int e, float ic) { return (int)(((float)e + 0.5f) * ic); }
 
 // G_K of a small supernode (c_L, c_U <= 64) into tileS[b][a] from its source
 // codes.  The threads walk the codes in storage order (both code arrays are
 // laid out in the order their side reads the panels), CH entries per thread
-// and round (every load of a round in flight together): 4 in FP64, so that
-// the kernel stays within the registers of four workgroups per compute unit
-// (one round up to 1024 entries), 8 in FP32 (up to 2048).
+// and round, every load of a round in flight together with the codes of the
+// next round: R rounds wait for R + 1 round trips.  4 in FP64, within the
+// registers of four workgroups per compute unit (8 entries: 34 for 32 us), 8 in FP32.
 template <typename T>
 __device__ __forceinline__ void gather_small_codes(const MatDev &M, int cl, int cu, int64_t c_off,
                                                    T (&tileS)[64][65]) {
@@ -290,14 +314,15 @@ __device__ __forceinline__ void gather_small_codes(const MatDev &M, int cl, int 
     const SELINV_GLOBAL T *ZL = gptr((const T *)M.ZL);
     const SELINV_GLOBAL T *ZU = gptr((const T *)M.ZU);
     const SELINV_GLOBAL double *Zd = gptr(M.Zd);
-    for (int base = 0; base < n; base += 256 * CH) {
-        uint32_t kl[CH], ku[CH];
+    const float icl = 1.0f / (float)cl, icu = 1.0f / (float)cu;
+    uint32_t kl[CH], ku[CH];
 #pragma unroll
-        for (int t = 0; t < CH; t++) {
-            const int e = base + tid + 256 * t, i = e < n ? e : 0;
-            kl[t] = cL[i];
-            ku[t] = cU[i];
-        }
+    for (int t = 0; t < CH; t++) {
+        const int i = min(tid + 256 * t, n - 1);
+        kl[t] = cL[i];
+        ku[t] = cU[i];
+    }
+    for (int base = 0; base < n; base += 256 * CH) {
         T vl[CH], vu[CH];
 #pragma unroll
         for (int t = 0; t < CH; t++) {
@@ -313,13 +338,21 @@ __device__ __forceinline__ void gather_small_codes(const MatDev &M, int cl, int 
             const uint32_t k3 = ku[t] >> GCODE_SHIFT, off3 = ku[t] & GCODE_MASK;
             vu[t] = ZU[k3 == 3 ? off3 : 0];
         }
+        uint32_t nl[CH], nu[CH];
 #pragma unroll
         for (int t = 0; t < CH; t++) {
-            const int e = base + tid + 256 * t;
-            if (e >= n) continue;
+            const int i = min(base + tid + 256 * (CH + t), n - 1);
+            nl[t] = cL[i];
+            nu[t] = cU[i];
+        }
+#pragma unroll
+        for (int t = 0; t < CH; t++) {
+            const int e = base + tid + 256 * t, ql = small_div(e, icl), qu = small_div(e, icu);
             const uint32_t k = kl[t] >> GCODE_SHIFT;
-            if (k == 1 || k == 2) tileS[e / cl][e % cl] = vl[t];
-            if ((ku[t] >> GCODE_SHIFT) == 3) tileS[e % cu][e / cu] = vu[t];
+            if (e < n && (k == 1 || k == 2)) tileS[ql][e - ql * cl] = vl[t];
+            if (e < n && (ku[t] >> GCODE_SHIFT) == 3) tileS[e - qu * cu][qu] = vu[t];
+            kl[t] = nl[t];
+            ku[t] = nu[t];
         }
     }
 }
@@ -332,7 +365,8 @@ __global__ __launch_bounds__(256, 4) void small_kernel(const MatDev *__restrict_
     __shared__ SmallSmem<T> sm;
     const SmallItem it = items[blockIdx.x];
     const int s = it.s, cl = it.cl, cu = it.cu;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15;
+    const int lane = threadIdx.x & 63, li = lane & 15;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // column block of this wavefront, and its share of the row blocks
     const int ns = (s + 15) / 16, per = 4 / ns;  // wavefronts per column block
     const bool active = wave < ns * per;
@@ -342,11 +376,14 @@ __global__ __launch_bounds__(256, 4) void small_kernel(const MatDev *__restrict_
     const GemmProb *pg4 = it.pg4 >= 0 ? &probs[it.pg4] : nullptr;
     SmallB<MODE> bL, bU;
     bL.load(pzu ? pzu->B : nullptr, pzu ? pzu->ldb : 1, s, cl, n0);
-    const GemmProb *pu = pzl ? pzl : pg4;  // Uhat: op(B) of steps 5 and 4
-    bU.load(pu ? pu->B : nullptr, pu ? pu->ldb : 1, s, cu, n0);
 
+    // zeros around G_K (the products read whole blocks of 16 k)
+    for (int b = wave; b < ((cu + 31) & ~31); b += 4)
+        if (lane >= cl || b >= cu) sm.g.tileS[b][lane] = (T)0;
     // (a small supernode with a non-empty G_K always has source codes)
     if (cl > 0 && cu > 0) gather_small_codes<T>(mats[it.mat], cl, cu, it.c_off, sm.g.tileS);
+    const GemmProb *pu = pzl ? pzl : pg4;  // Uhat: op(B) of steps 5 and 4
+    bU.load(pu ? pu->B : nullptr, pu ? pu->ldb : 1, s, cu, n0);
     __syncthreads();
     T(&G)[64][65] = sm.g.tileS;  // G[b][a] = G_K(a, b), later zu[b][j]
     // step 3: A^{-T}(K,R_U)^T = -G^T Lhat (cu x s); the wavefront's tiles stay
@@ -359,7 +396,7 @@ __global__ __launch_bounds__(256, 4) void small_kernel(const MatDev *__restrict_
             for (int i = 0; i < 4; i++) {
                 const int mb = mfirst + i * per;
                 if (16 * mb >= cu) break;
-                zacc[i] = bL.tile([&](int m, int k) { return G[m][k]; }, cu, cl, 16 * mb);
+                zacc[i] = bL.tile([&](int m, int k) { return G[m][k]; }, cl, 16 * mb);
                 const int m = 16 * mb + li;
 #pragma unroll
                 for (int v = 0; v < 4; v++) {
@@ -373,7 +410,7 @@ __global__ __launch_bounds__(256, 4) void small_kernel(const MatDev *__restrict_
         if (pzl) {
             SELINV_GLOBAL T *C = gptr_w((T *)pzl->C);
             for (int mb = mfirst; 16 * mb < cl; mb += per) {
-                const typename MF::Acc acc = bU.tile([&](int m, int k) { return G[k][m]; }, cl, cu, 16 * mb);
+                const typename MF::Acc acc = bU.tile([&](int m, int k) { return G[k][m]; }, cu, 16 * mb);
                 const int m = 16 * mb + li;
 #pragma unroll
                 for (int v = 0; v < 4; v++) {
@@ -382,6 +419,19 @@ __global__ __launch_bounds__(256, 4) void small_kernel(const MatDev *__restrict_
                     C[m + (int64_t)c * pzl->ldc] = (T)(pzl->alpha * (double)acc[v]);
                 }
             }
+        }
+    }
+    // the initial A^{-T}(K,K) of all of this wavefront's row blocks in flight
+    // together (clamped addresses) over the barriers and the products
+    double cin[4][4];
+    if (active && pg4) {
+        const SELINV_GLOBAL double *C = gptr((const double *)pg4->C);
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            if (16 * (mfirst + i * per) >= s) break;
+            const int m = min(16 * (mfirst + i * per) + li, s - 1);
+#pragma unroll
+            for (int v = 0; v < 4; v++) cin[i][v] = C[m + (int64_t)min(n0 + MF::col(lane, v), s - 1) * pg4->ldc];
         }
     }
     __syncthreads();
@@ -403,20 +453,11 @@ __global__ __launch_bounds__(256, 4) void small_kernel(const MatDev *__restrict_
     // step 4: A^{-T}(K,K) -= A^{-T}(K,R_U) Uhat^T (FP64 accumulation)
     if (active && pg4) {
         SELINV_GLOBAL double *C = gptr_w((double *)pg4->C);
-        // the initial A^{-T}(K,K) of all of this wavefront's row blocks in
-        // flight together (clamped addresses), then the products
-        double cin[4][4];
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const int m = min(16 * (mfirst + i * per) + li, s - 1);
-#pragma unroll
-            for (int v = 0; v < 4; v++) cin[i][v] = C[m + (int64_t)min(n0 + MF::col(lane, v), s - 1) * pg4->ldc];
-        }
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             const int mb = mfirst + i * per;
             if (16 * mb >= s) break;
-            const typename MF::Acc acc = bU.tile([&](int m, int k) { return G[k][m]; }, s, cu, 16 * mb);
+            const typename MF::Acc acc = bU.tile([&](int m, int k) { return G[k][m]; }, cu, 16 * mb);
             const int m = 16 * mb + li;
 #pragma unroll
             for (int v = 0; v < 4; v++) {

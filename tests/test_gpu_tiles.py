@@ -206,3 +206,33 @@ def test_gather_tiles_of_one_supernode(n, density, cap, prec):
     assert np.abs(got[0][k] - ref).max() / np.abs(ref).max() <= TOL[prec]
     for x in got[1:]:
         assert np.array_equal(x, got[0])
+
+
+# small supernodes handled whole by one workgroup: operand edges at and beside
+# the blocks of 16 (k and rows) and 32 (split-BF16 k chunks), against the
+# per-phase launches bit for bit and the oracle
+@pytest.mark.parametrize("n,density,cap", [(2, 1.0, 1), (17, 1.0, 16), (33, 1.0, 17), (49, 1.0, 15), (65, 1.0, 1),
+                                           (80, 1.0, 33), (97, 1.0, 48), (127, 1.0, 63), (128, 1.0, 64),
+                                           (120, 0.02, 64), (128, 0.02, 5)])
+@pytest.mark.parametrize("prec", ["fp64", "mixed_fp32", "mixed_bf16x3"])
+def test_small_supernodes_equal_the_per_phase_launches(n, density, cap, prec):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_1708_04539_amd import selinv as si
+    print("[case] small supernodes", n, density, cap, prec, flush=True)
+    cp, ri, v, _ = random_sparse(n, density, 7)
+    s = si.SelInv(n, cp, ri, None, cap, 0, 100)
+    s.factor(v)
+    s.run(prec)
+    assert sum(s.level_stats(d)["small_count"] for d in range(s.info["nlevels"])) > 0
+    r, c, x = s.export(sort=False)
+    s.set_tuning(table(s.info["nlevels"], 32), prec)
+    s.run(prec)
+    assert sum(s.level_stats(d)["small_count"] for d in range(s.info["nlevels"])) == 0
+    assert np.array_equal(s.export(sort=False)[2], x)
+    s.close()
+    r2, c2, ref = Oracle(n, cp, ri, None, cap, 0, 0, 100).factor(v).selinv().export()
+    k = np.lexsort((r, c))
+    assert np.array_equal(r[k], r2) and np.array_equal(c[k], c2)
+    assert np.abs(x[k] - ref).max() / np.abs(ref).max() <= TOL[prec]
