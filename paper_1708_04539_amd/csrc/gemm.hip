@@ -8,15 +8,17 @@
 // different shapes (all supernodes of one level, of every matrix of a batch).
 // Tile BM x BN (128x128, 64x64 or 32x32) per workgroup of 256 threads = 4
 // wavefronts in a 2x2 arrangement, each wavefront owning a (BM/2)x(BN/2)
-// block made of 16x16 MFMA tiles.  The k loop is software pipelined: the next k-chunk is
-// loaded from global memory into registers while the current one is consumed
-// from LDS, and LDS is double buffered (one barrier per chunk).
+// block made of 16x16 MFMA tiles.  LDS is double buffered, one barrier per
+// k chunk: the 64- and 128-wide tiles of the large products load the next chunk
+// from global memory straight into LDS (gemm_tile_dma), the others into
+// registers while the current one is consumed (gemm_tile).
 //
 // Arithmetic modes
 //   CMP_F64     v_mfma_f64_16x16x4, FP64 operands and accumulation.
 //   CMP_F32     v_mfma_f32_16x16x4, FP32 operands and accumulation.
-//   CMP_BF16X3  both operands split once, when staged into LDS, into
-//               x = hi + lo with hi = bf16(x) and lo = bf16(x - hi); the
+//   CMP_BF16X3  both operands as x = hi + lo with hi = bf16(x) and
+//               lo = bf16(x - hi), split where they are written (G, Lhat, Uhat)
+//               or, for FP32 and FP64 operands, when staged into LDS; the
 //               product is hi*hi + hi*lo + lo*hi on v_mfma_f32_16x16x32_bf16
 //               with FP32 accumulation (the lo*lo term is dropped).
 // The MFMA is fed with op(B) as its first operand and op(A) as its second,
@@ -31,11 +33,6 @@
 
 namespace selinv {
 
-// LDS stages of the tiles that load straight into LDS
-template <int MODE, int BM>
-struct DmaStages {
-    static constexpr int value = 2;
-};
 // Tiles of a product that take gemm_tile_dma: both operands in the type of the
 // arrays that only products read, 64 wide (FP32 and split-BF16 also 128 wide;
 // 128-wide FP64 tiles leave it no registers).  The 32-wide tiles serve launches
@@ -54,13 +51,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BM == 128 ?
     // op(B) is a normalised panel, but in the prologue's products
     typedef std::conditional_t<ROLE == 0, TA, typename Mode<MODE>::G> TB;
     constexpr bool D = kDmaTile<MODE, BM, TA>;
-    typedef std::conditional_t<D, DmaSmem<BM, BN, DmaStages<MODE, BM>::value>, Smem<MODE, BM, BN>> SM;
+    typedef std::conditional_t<D, DmaSmem<BM, BN>, Smem<MODE, BM, BN>> SM;
     __shared__ SM sm;
     const GemmTile tl = tiles[xcd_tile(blockIdx.x, gridDim.x)];
     // only the step-4 product accumulates into an input matrix
     auto tile = [&](int n0) __attribute__((always_inline)) {
         if constexpr (D)
-            gemm_tile_dma<MODE, BM, BN, DmaStages<MODE, BM>::value, TC, ROLE == 2>(probs[tl.prob], tl.m0, n0, sm);
+            gemm_tile_dma<MODE, BM, BN, TC, ROLE == 2>(probs[tl.prob], tl.m0, n0, sm);
         else
             gemm_tile<MODE, BM, BN, TA, TB, TC, ROLE == 2>(probs[tl.prob], tl.m0, n0, sm);
     };
@@ -129,7 +126,7 @@ __global__ __launch_bounds__(256) void step4_gather(const GemmProb *__restrict__
                                                     const GatherTile *__restrict__ gtiles) {
     constexpr bool D = kDmaTile<MODE, BM, TA>;
     union Shared {
-        std::conditional_t<D, DmaSmem<BM, BN, DmaStages<MODE, BM>::value>, Smem<MODE, BM, BN>> g;
+        std::conditional_t<D, DmaSmem<BM, BN>, Smem<MODE, BM, BN>> g;
         GatherSmem<TA> t;
     };
     __shared__ Shared sm;
@@ -137,7 +134,7 @@ __global__ __launch_bounds__(256) void step4_gather(const GemmProb *__restrict__
     if (b < ntiles) {
         const GemmTile tl = tiles[xcd_tile(b, ntiles)];
         if constexpr (D)
-            gemm_tile_dma<MODE, BM, BN, DmaStages<MODE, BM>::value, double, true, true>(probs[tl.prob], tl.m0, tl.n0,
+            gemm_tile_dma<MODE, BM, BN, double, true, true>(probs[tl.prob], tl.m0, tl.n0,
                                                                                        sm.g, mats);
         else
             gemm_tile<MODE, BM, BN, TA, typename Mode<MODE>::G, double, true, true>(probs[tl.prob], tl.m0, tl.n0,

@@ -202,7 +202,7 @@ __global__ __launch_bounds__(256) void schur_scatter_kernel(const MatDev *__rest
                                                             const GatherTile *__restrict__ tiles, double *diag,
                                                             double *lpan, double *upan) {
     union Shared {
-        DmaSmem<64, 64, 2> g;
+        DmaSmem<64, 64> g;
         double t[64][65];  // [b][a]
     };
     __shared__ Shared sm;
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(256) void schur_scatter_kernel(const MatDev *__rest
         p.K = sn[K].s;
         p.ktri = p.cpx = 0;
         AccTile<CMP_F64, 64, 64> w;
-        DmaProduct<CMP_F64, 64, 64, 2, 0, 1>::form(p, a0, b0, sm.g, w);
+        DmaProduct<CMP_F64, 64, 64, 0, 1>::form(p, a0, b0, sm.g, w);
         __syncthreads();  // LDS free for the tile
         const int lane = tid & 63, wave = tid >> 6;
 #pragma unroll

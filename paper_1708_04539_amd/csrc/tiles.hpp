@@ -781,7 +781,7 @@ __device__ __forceinline__ void gemm_tile_g35(const GemmProb &p, const int m0, c
 //   contiguous along the rows: row k of the chunk holds its R elements at
 //     k * R * E, byte m * E at (m * E) ^ ((k & 3) * 16 E): the four k of an
 //     operand read fall on different bank groups.
-// ST LDS stages: chunk c + ST - 1 is issued after the barrier that ends chunk
+// Two LDS stages: chunk c + 1 is issued after the barrier that ends chunk
 // c - 1, one barrier per chunk.  Rows past the operand are read as its last
 // row (k-contiguous) or as whatever follows them, zeros past the operand's end
 // (the buffer's range); they only reach results that are not stored.  The k
@@ -789,9 +789,9 @@ __device__ __forceinline__ void gemm_tile_g35(const GemmProb &p, const int m0, c
 // up to the next multiple of 4; the MFMAs beyond are left out.  The products
 // are those of the register-staged tile in the same order, so the results are
 // equal bit for bit.
-template <int BM, int BN, int ST>
+template <int BM, int BN>
 struct DmaSmem {
-    alignas(128) char b[ST][(BM + BN) * 128];
+    alignas(128) char b[2][(BM + BN) * 128];
 };
 
 typedef __attribute__((address_space(3))) char lds_char;
@@ -868,10 +868,9 @@ struct DmaOperand {
     }
 };
 
-// Waits for this wavefront's loads but the last N, and for every wavefront's.
-template <int N>
+// Waits for this wavefront's loads, and for every wavefront's.
 __device__ __forceinline__ void dma_barrier() {
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
 // acc = op(A) op(B) of the BM x BN tile at (m0, n0), in the accumulators of
@@ -880,15 +879,14 @@ template <int MODE, int BM, int BN>
 struct AccTile {
     typename Mode<MODE>::Acc a[BM / 32][BN / 32];
 };
-template <int MODE, int BM, int BN, int ST, int OPA, int OPB>
+template <int MODE, int BM, int BN, int OPA, int OPB>
 struct DmaProduct {
     static __device__ __forceinline__ void form(const GemmProb &p, const int m0, const int n0,
-                                                DmaSmem<BM, BN, ST> &sm, AccTile<MODE, BM, BN> &t) {
+                                                DmaSmem<BM, BN> &sm, AccTile<MODE, BM, BN> &t) {
         typedef typename Mode<MODE>::G T;
         typedef typename Mode<MODE>::Acc Acc;
         constexpr bool PK = MODE == CMP_BF16X3;
         auto &acc = t.a;
-        static_assert(ST == 2 || ST == 3, "stages");
         typedef DmaOperand<T, BM, OPA == 1> OA;
         typedef DmaOperand<T, BN, OPB == 0> OB;
         constexpr int BK = OA::BK, WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
@@ -924,7 +922,9 @@ struct DmaProduct {
         for (int q = 0; q < (OPB == 0 ? NU : TN); q++)
             ob[q] = BM * 128 + (OPB == 0 ? OB::at(wn * WN + li, PK ? 8 * lk + 4 * q : 4 * q + lk)
                                          : OB::at(wn * WN + 16 * q + li, PK ? 8 * lk : lk));
-        auto kstep = [&](int st, int q) {
+        // (of the first NM x NN blocks of 16 rows and columns)
+        auto kstep = [&](int st, int q, auto NM_, auto NN_) {
+            constexpr int NM = decltype(NM_)::value, NN = decltype(NN_)::value;
             if constexpr (PK) {
                 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
                 // tile i of an operand: the words of 8 k, parted into hi and lo
@@ -954,37 +954,37 @@ struct DmaProduct {
                     hi = __builtin_bit_cast(v8bf, h);
                     lo = __builtin_bit_cast(v8bf, l);
                 };
-                v8bf bh[TN], bl[TN];
+                v8bf bh[NN], bl[NN];
 #pragma unroll
-                for (int j = 0; j < TN; j++)
+                for (int j = 0; j < NN; j++)
                     frag(std::integral_constant<bool, OPB == 0>{}, ob, j, OB::RB, bh[j], bl[j]);
 #pragma unroll
-                for (int i = 0; i < TM; i++) {
+                for (int i = 0; i < NM; i++) {
                     v8bf ah, al;
                     frag(std::integral_constant<bool, OPA == 1>{}, oa, i, OA::RB, ah, al);
 #pragma unroll
-                    for (int j = 0; j < TN; j++) {
+                    for (int j = 0; j < NN; j++) {
                         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl[j], ah, acc[i][j], 0, 0, 0);
                         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], al, acc[i][j], 0, 0, 0);
                         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bh[j], ah, acc[i][j], 0, 0, 0);
                     }
                 }
             } else {
-                T av[TM], bv[TN];
+                T av[NM], bv[NN];
 #pragma unroll
-                for (int i = 0; i < TM; i++)
+                for (int i = 0; i < NM; i++)
                     av[i] = *(const __attribute__((address_space(3))) T *)(lds + (OPA == 1 ? oa[q] : oa[i]) +
                                                                            (st * SB +
                                                                             (OPA == 1 ? i * 16 * 128 : 4 * q * OA::RB)));
 #pragma unroll
-                for (int j = 0; j < TN; j++)
+                for (int j = 0; j < NN; j++)
                     bv[j] = *(const __attribute__((address_space(3))) T *)(lds + (OPB == 0 ? ob[q] : ob[j]) +
                                                                            (st * SB +
                                                                             (OPB == 0 ? j * 16 * 128 : 4 * q * OB::RB)));
 #pragma unroll
-                for (int i = 0; i < TM; i++)
+                for (int i = 0; i < NM; i++)
 #pragma unroll
-                    for (int j = 0; j < TN; j++) {
+                    for (int j = 0; j < NN; j++) {
                         if constexpr (MODE == CMP_F64)
                             acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(bv[j], av[i], acc[i][j], 0, 0, 0);
                         else
@@ -996,75 +996,94 @@ struct DmaProduct {
         // structure are skipped, as in gemm_tile_op
         const int klo = max((p.ktri & 1) ? (p.cpx ? 2 * n0 : n0) : 0, (p.ktri & 2) ? m0 : 0);
         const int nch = (K + BK - 1) / BK, nfull = K / BK, c0 = min(klo / BK, nch);
-        constexpr int NI = OA::NI + OB::NI;  // loads per wavefront and chunk
         if (c0 < nch) issue(c0, 0);
-        if constexpr (ST == 3) {
-            if (c0 + 1 < nch) issue(c0 + 1, 1);
-        }
         // chunk c (stage S) has landed everywhere and chunk c - 1 is used up
         auto arrive = [&](int c, int S) {
-            if (ST == 3 && c + 1 < nch)
-                dma_barrier<(ST == 3 ? NI : 0)>();
-            else
-                dma_barrier<0>();
-            if (c + ST - 1 < nch) issue(c + ST - 1, (S + ST - 1) % ST);
-        };
-        auto step = [&](int c, auto S_) {
-            constexpr int S = decltype(S_)::value;
-            arrive(c, S);
-#pragma unroll
-            for (int q = 0; q < KS; q++) kstep(S, q);
+            dma_barrier();
+            if (c + 1 < nch) issue(c + 1, 1 - S);
         };
         typedef std::integral_constant<int, 0> S0;
         typedef std::integral_constant<int, 1> S1;
-        typedef std::integral_constant<int, ST - 1> SL;
-        for (int c = c0; c < nfull; c += ST) {
-            step(c, S0{});
-            if (c + 1 < nfull) step(c + 1, S1{});
-            if constexpr (ST == 3) {
-                if (c + 2 < nfull) step(c + 2, SL{});
-            }
-        }
-        if (max(c0, nfull) < nch) {
-            // last, partial chunk
-            const int S = max(nfull - c0, 0) % ST;
-            arrive(nch - 1, S);
-            constexpr int KM = PK ? BK : 4;  // k of one MFMA
-            const int kr = K - nfull * BK, nz = (KM - kr % KM) % KM;
-            for (int e = threadIdx.x; e < nz * (BM + BN); e += 256) {
-                const int k = kr + e / (BM + BN), r = e % (BM + BN);
-                const int o = r < BM ? OA::at(r, k) : BM * 128 + OB::at(r - BM, k);
-                *(__attribute__((address_space(3))) raw_t<T> *)(lds + S * SB + o) = 0;
-            }
-            dma_barrier<0>();
+        auto run = [&](auto NM, auto NN) {
+            auto step = [&](int c, auto S_) {
+                constexpr int S = decltype(S_)::value;
+                arrive(c, S);
+                if constexpr (decltype(NM)::value > 0) {
 #pragma unroll
-            for (int q = 0; q < KS; q++)
-                if (KM * q < kr) kstep(S, q);
-        }
+                    for (int q = 0; q < KS; q++) kstep(S, q, NM, NN);
+                }
+            };
+            for (int c = c0; c < nfull; c += 2) {
+                step(c, S0{});
+                if (c + 1 < nfull) step(c + 1, S1{});
+            }
+            if (max(c0, nfull) < nch) {
+                // last, partial chunk
+                const int S = max(nfull - c0, 0) % 2;
+                arrive(nch - 1, S);
+                constexpr int KM = PK ? BK : 4;  // k of one MFMA
+                const int kr = K - nfull * BK, nz = (KM - kr % KM) % KM;
+                for (int e = threadIdx.x; e < nz * (BM + BN); e += 256) {
+                    const int k = kr + e / (BM + BN), r = e % (BM + BN);
+                    const int o = r < BM ? OA::at(r, k) : BM * 128 + OB::at(r - BM, k);
+                    *(__attribute__((address_space(3))) raw_t<T> *)(lds + S * SB + o) = 0;
+                }
+                dma_barrier();
+                if constexpr (decltype(NM)::value > 0) {
+#pragma unroll
+                    for (int q = 0; q < KS; q++)
+                        if (KM * q < kr) kstep(S, q, NM, NN);
+                }
+            }
+        };
+        typedef std::integral_constant<int, TM> FM;
+        typedef std::integral_constant<int, TN> FN;
+        typedef std::integral_constant<int, TM / 2> HM;
+        typedef std::integral_constant<int, TN / 2> HN;
+        // Rows and columns of the wavefront's part that exist.  A part with at
+        // most half of them skips the other half's products (the loads and
+        // barriers stay): a 64-wide tile at the edge of a 70-row operand issues
+        // a quarter of its MFMAs, none in two of its wavefronts.  12 small 2D
+        // systems 664 -> 654 us, 48^3 FP64 7602 -> 7485, 45x38x31 FP32
+        // 1221 -> 1203; 64^3, with few edges, the same.  128-wide tiles are
+        // taken only where little of their area is edge.
+        const int rm = p.M - m0 - wm * WM, rn = p.N - n0 - wn * WN;
+        if constexpr (BM == 128)
+            run(FM{}, FN{});
+        else if (rm > WM / 2 && rn > WN / 2)
+            run(FM{}, FN{});
+        else if (rm <= 0 || rn <= 0)
+            run(S0{}, S0{});
+        else if (rm > WM / 2)
+            run(FM{}, HN{});
+        else if (rn > WN / 2)
+            run(HM{}, FN{});
+        else
+            run(HM{}, HN{});
     }
 };
 
-template <int MODE, int BM, int BN, int ST, typename TC, bool CIN, int OPA, int OPB, bool PUSH>
+template <int MODE, int BM, int BN, typename TC, bool CIN, int OPA, int OPB, bool PUSH>
 __device__ __forceinline__ void gemm_tile_dma_op(const GemmProb &p, const int m0, const int n0,
-                                                 DmaSmem<BM, BN, ST> &sm, const MatDev *mats) {
+                                                 DmaSmem<BM, BN> &sm, const MatDev *mats) {
     AccTile<MODE, BM, BN> t;
-    DmaProduct<MODE, BM, BN, ST, OPA, OPB>::form(p, m0, n0, sm, t);
+    DmaProduct<MODE, BM, BN, OPA, OPB>::form(p, m0, n0, sm, t);
     gemm_store<MODE, BM, BN, TC, CIN, PUSH, typename Mode<MODE>::G>(p, m0, n0, t.a, mats);
 }
 
-template <int MODE, int BM, int BN, int ST, typename TC, bool CIN, bool PUSH = false>
-__device__ __forceinline__ void gemm_tile_dma(const GemmProb &p, const int m0, const int n0, DmaSmem<BM, BN, ST> &sm,
+template <int MODE, int BM, int BN, typename TC, bool CIN, bool PUSH = false>
+__device__ __forceinline__ void gemm_tile_dma(const GemmProb &p, const int m0, const int n0, DmaSmem<BM, BN> &sm,
                                               const MatDev *mats = nullptr) {
     if (p.opA == 0) {
         if (p.opB == 0)
-            gemm_tile_dma_op<MODE, BM, BN, ST, TC, CIN, 0, 0, PUSH>(p, m0, n0, sm, mats);
+            gemm_tile_dma_op<MODE, BM, BN, TC, CIN, 0, 0, PUSH>(p, m0, n0, sm, mats);
         else
-            gemm_tile_dma_op<MODE, BM, BN, ST, TC, CIN, 0, 1, PUSH>(p, m0, n0, sm, mats);
+            gemm_tile_dma_op<MODE, BM, BN, TC, CIN, 0, 1, PUSH>(p, m0, n0, sm, mats);
     } else {
         if (p.opB == 0)
-            gemm_tile_dma_op<MODE, BM, BN, ST, TC, CIN, 1, 0, PUSH>(p, m0, n0, sm, mats);
+            gemm_tile_dma_op<MODE, BM, BN, TC, CIN, 1, 0, PUSH>(p, m0, n0, sm, mats);
         else
-            gemm_tile_dma_op<MODE, BM, BN, ST, TC, CIN, 1, 1, PUSH>(p, m0, n0, sm, mats);
+            gemm_tile_dma_op<MODE, BM, BN, TC, CIN, 1, 1, PUSH>(p, m0, n0, sm, mats);
     }
 }
 

@@ -38,6 +38,7 @@ SIZES = [
     (65, 63, 64, 1),
     (64, 129, 127, 2),
     (200, 3, 130, 61),
+    (48, 80, 112, 16, 96),
 ]
 
 
