@@ -282,7 +282,9 @@ selinv_status selinv_set_gather_form(selinv_handle h, int32_t form);
  * Each configuration runs reps + 1 times (the first untimed; 1 <= reps <=
  * 100) and counts its fastest run: per-launch times from eager runs with
  * events, whole-sweep comparisons from replays of the sweep's HIP graph.  When the measured choices are not faster
- * than the built-in size policy, the policy is kept.  ms_policy and ms_tuned
+ * than the built-in size policy, the policy is kept: the table then has tile
+ * edges 0 and the prologue placement and in-place levels that the policy
+ * takes without a table.  ms_policy and ms_tuned
  * (nullable) receive the two sweep times.  Needs a factored handle; the runs
  * leave the results of an ordinary run behind.  Batches have their own
  * tables (selinv_batch_tune). */

@@ -2403,6 +2403,18 @@ static selinv_status runner_tune(Runner &R, int prec, int32_t reps, hipStream_t 
     R.tune[prec] = Tuning();
     double t_policy = 0, t = 0;
     if ((st = tune_measure(R, prec, s, reps, false, t_policy, nullptr, err))) return st;
+    // The same choices as a table: tile edges 0, the prologue where the policy
+    // puts it, the levels it reads in place.  (Such a table fixes the last two,
+    // so all zeros would be other choices.)
+    Tuning pol;
+    pol.set = true;
+    pol.t35.assign(L, 0);
+    pol.t4.assign(L, 0);
+    pol.no_small.assign(L, 0);
+    pol.no_fork = R.sweep[prec]->split > 0 ? 0 : 1;
+    // (a forced gather form hides the levels of form 0)
+    pol.vg = R.gather_form == 0 ? R.sweep[prec]->vg : in_place_levels(R.hs, prec);
+    pol.vg.resize(L, 0);
 
     // 1. tile edge of every launch class: the whole level sweep profiled once
     //    per candidate edge, every class keeps its fastest edge
@@ -2540,12 +2552,6 @@ static selinv_status runner_tune(Runner &R, int prec, int32_t reps, hipStream_t 
     }
     // 6. keep the size policy when the measured choices are no faster
     if (t_best > t_policy) {
-        Tuning pol;
-        pol.set = true;
-        pol.t35.assign(L, 0);
-        pol.t4.assign(L, 0);
-        pol.no_small.assign(L, 0);
-        pol.vg.assign(L, 0);
         best = pol;
         t_best = t_policy;
     }
