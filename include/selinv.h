@@ -246,10 +246,11 @@ selinv_status selinv_set_sweep_mode(selinv_handle h, int32_t mode);
  *     of steps 3 and 5 then read;
  *   2: no stored G on any level of large supernodes: the products of steps
  *     3 and 5 read every entry of G_K from the diagonal block, L panel or U
- *     panel that holds it, through a 32-bit source code per entry (built on
- *     the first such run, c_L c_U codes per supernode, 4 bytes each, in
- *     device memory from the handle's allocator; SELINV_E_NOMEM when that
- *     fails).  Levels run by the fused small-supernode launch keep G_K in
+ *     panel that holds it, through a 32-bit source code per entry: the
+ *     gather codes of a plan whose every G_K has them
+ *     (selinv_set_gather_code_budget), else codes built on the first such
+ *     run, c_L c_U per supernode, 4 bytes each, in device memory from the
+ *     handle's allocator (SELINV_E_NOMEM when that fails).  Levels run by the fused small-supernode launch keep G_K in
  *     LDS, and the persistent sweep always gathers into G.
  * The results of forms 1 and 2 are equal bit for bit (the same values in the
  * same order).  form outside 0..2: SELINV_E_INVALID_ARG.  Changing the form

@@ -39,12 +39,13 @@ struct MatDev {
     const int64_t *push_off;
     const int32_t *push_pos;
     // precomputed source codes of the gather (supernodes with c_off >= 0):
-    // gcL[c_off + a + b cl] for the diagonal-block and L-side entries,
-    // gcU[c_off + b + a cu] for the U-side entries of G_K(a, b)
+    // gcL[c_off + a + b cl] for every entry G_K(a, b), gcU[c_off + b + a cu]
+    // again for the U-side ones (0 elsewhere)
     const uint32_t *gcL, *gcU;
-    // source codes of every entry of G_K in the layout of G_K itself (all
-    // three arrays, gcA[ca_off(K) + a + b c_L]), read by the step-3/5 products
-    // that take G_K from its sources instead of a stored G (GemmProb::gcode)
+    // source codes of every entry of G_K in the layout of G_K itself
+    // (gcA[ca_off(K) + a + b c_L]; gcL where every supernode has codes), read by
+    // the step-3/5 products that take G_K from its sources instead of a stored
+    // G (GemmProb::gcode)
     const uint32_t *gcA;
     // where the rows and columns of every G_K come from, per entry of rl / ru
     // (index rl_off(K) + a, ru_off(K) + b).  Row r: its supernode I (row_I)

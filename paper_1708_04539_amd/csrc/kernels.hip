@@ -233,38 +233,6 @@ __global__ __launch_bounds__(256) void gather_kernel(const MatDev *__restrict__ 
     gather_tile<T, TG>(mats[tl.mat], tl, sm);
 }
 
-// The two source-code arrays of the gather (MatDev::gcL in G's column order,
-// gcU in its row order, each with zeros at the other's entries) merged into one
-// in the layout of G_K (MatDev::gcA), for a plan whose every G_K has codes:
-// supernode blockIdx.x, its 64x64 tiles dealt over blockIdx.y; the U-side codes
-// are transposed through LDS.  Once per handle, and bound by its 12 bytes a
-// code; forming them again on the host and copying them took 10 ms where this
-// takes 20 us (2D 256^2, 7.2 million codes).
-__global__ __launch_bounds__(256) void merge_codes_kernel(const SnRec *__restrict__ sn,
-                                                          const uint32_t *__restrict__ gcL,
-                                                          const uint32_t *__restrict__ gcU,
-                                                          uint32_t *__restrict__ gcA) {
-    __shared__ uint32_t u[64][65];  // [a][b]
-    const SnRec r = sn[blockIdx.x];
-    if (r.c_off < 0) return;
-    const int ta = (r.cl + 63) / 64, tb = (r.cu + 63) / 64;
-    const int e0 = threadIdx.x & 63, e1 = threadIdx.x >> 6;
-    for (int64_t t = blockIdx.y; t < (int64_t)ta * tb; t += gridDim.y) {
-        const int a0 = 64 * (int)(t % ta), b0 = 64 * (int)(t / ta);
-        for (int a = e1; a < 64; a += 4)
-            if (a0 + a < r.cl && b0 + e0 < r.cu)
-                u[a][e0] = gptr(gcU)[r.c_off + (b0 + e0) + (int64_t)(a0 + a) * r.cu];
-        __syncthreads();
-        for (int b = e1; b < 64; b += 4)
-            if (a0 + e0 < r.cl && b0 + b < r.cu) {
-                const int64_t i = r.c_off + (a0 + e0) + (int64_t)(b0 + b) * r.cl;
-                const uint32_t l = gptr(gcL)[i];
-                gptr_w(gcA)[i] = l ? l : u[e0][b];
-            }
-        __syncthreads();
-    }
-}
-
 // ---------------------------------------------------------------------------
 // split-K reduction of the step-4 products
 // ---------------------------------------------------------------------------
@@ -364,13 +332,6 @@ hipError_t launch_gather(int mode, const MatDev *mats, const GatherTile *tiles, 
         hipLaunchKernelGGL((gather_kernel<float, float>), dim3(ntiles), dim3(256), 0, st, mats, tiles);
     else
         hipLaunchKernelGGL((gather_kernel<float, Pk32>), dim3(ntiles), dim3(256), 0, st, mats, tiles);
-    return hipGetLastError();
-}
-
-hipError_t launch_merge_codes(const SnRec *sn, int count, const uint32_t *gcL, const uint32_t *gcU, uint32_t *gcA,
-                              hipStream_t st) {
-    if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(merge_codes_kernel, dim3(count, 8), dim3(256), 0, st, sn, gcL, gcU, gcA);
     return hipGetLastError();
 }
 

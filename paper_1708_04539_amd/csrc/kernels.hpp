@@ -44,9 +44,6 @@ hipError_t launch_step4_gather(int mode, int tile, const GemmProb *probs, const 
 // gather + steps 3/5 + step 4 of small supernodes, one workgroup each (persist.hip)
 hipError_t launch_small(int mode, const MatDev *mats, const GemmProb *probs, const SmallItem *items, int count,
                         hipStream_t st);
-// gcA (one code per entry of every G_K, at c_off) from gcL and gcU
-hipError_t launch_merge_codes(const SnRec *sn, int count, const uint32_t *gcL, const uint32_t *gcU, uint32_t *gcA,
-                              hipStream_t st);
 hipError_t launch_extract(int f64, const ExtractArgs &a, hipStream_t st);
 // C += sum of the split-K partial products, for `count` items (count <= 65535),
 // pushing the results into the children's G where an item asks for it

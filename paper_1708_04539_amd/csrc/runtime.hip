@@ -292,9 +292,10 @@ struct selinv_handle_s {
     std::vector<uint32_t> gcL, gcU;
     uint32_t *d_gcL = nullptr, *d_gcU = nullptr;
     // codes of every G_K in the layout of G_K (MatDev::gcA) for the products
-    // that read G_K from its sources: built on first use (ca_state 0 not yet,
-    // 1 built, -1 unavailable: offsets beyond the code's 30 bits); ca_off[K]
-    // its first code (-1: c_L or c_U is 0), ca_total the code count
+    // that read G_K from its sources: gcL where every G_K has gather codes,
+    // else d_gcA, built on first use (ca_state 0 not yet, 1 there, -1
+    // unavailable: offsets beyond the code's 30 bits); ca_off[K] its first code
+    // (-1: c_L or c_U is 0), ca_total the code count
     std::vector<int64_t> ca_off;
     int64_t ca_total = 0;
     uint32_t *d_gcA = nullptr;
@@ -560,7 +561,7 @@ bool all_coded(selinv_handle h);
 inline bool fused_prologue(const SnRec &r) { return r.s <= 64 && r.cl <= 64 && r.cu <= 64; }
 
 // Levels whose steps 3/5 read G_K from its sources without a tuning: only where
-// every G_K of the plan has gather codes (their merge takes microseconds), and
+// every G_K of the plan has gather codes (nothing is built or allocated), and
 // where a stored G gains nothing from being read again, that is where the
 // products read it once (s up to one tile).  A launch of 32-wide tiles waits
 // for its loads either way, and the gather and the push it saves count; FP64
@@ -699,7 +700,7 @@ selinv_status build_sweep(std::vector<selinv_handle> &hs, const DevAlloc &al, in
         m.push_pos = h->d_push_pos;
         m.gcL = h->d_gcL;
         m.gcU = h->d_gcU;
-        m.gcA = h->d_gcA;
+        m.gcA = h->d_gcA ? h->d_gcA : h->d_gcL;
         m.row_I = h->d_row_I;
         m.row_up = h->d_row_up;
         m.col_J = h->d_col_J;
@@ -1587,26 +1588,23 @@ void build_gather_codes(const Plan &P, std::vector<SnRec> &sn, std::vector<uint3
             const int32_t c = P.ru[P.ru_ptr[K] + b], J = P.supof[c], fJ = P.xsup[J];
             for (int64_t a = 0; a < cl; a++) {
                 const uint32_t code = gcode_of(P, K, a, b, c, J, fJ);
-                if ((code >> GCODE_SHIFT) == 3)
-                    gcU[co + b + a * cu] = code;
-                else
-                    gcL[co + a + b * cl] = code;
+                gcL[co + a + b * cl] = code;
+                if ((code >> GCODE_SHIFT) == 3) gcU[co + b + a * cu] = code;
             }
         }
     }
 }
 
-// Every non-empty G_K has gather codes (gcL, gcU).
+// Every non-empty G_K has gather codes (c_off >= 0).
 bool all_coded(selinv_handle h) {
     for (const SnRec &r : h->sn)
         if (r.cl > 0 && r.cu > 0 && r.c_off < 0) return false;
     return true;
 }
 
-// The codes of every G_K in its own layout (MatDev::gcA), built once per
-// handle on first use: merged on the device where every G_K has gather codes,
-// else filled by up to 16 host threads over the supernodes, uploaded, and the
-// host copy released.
+// The codes of every G_K in its own layout (MatDev::gcA): gcL where every G_K
+// has gather codes; else built once per handle on first use, filled by up to 16
+// host threads over the supernodes, uploaded, and the host copy released.
 selinv_status ensure_codes_all(selinv_handle h) {
     if (h->ca_state != 0) return SELINV_OK;
     const Plan &P = h->P;
@@ -1616,21 +1614,18 @@ selinv_status ensure_codes_all(selinv_handle h) {
         return SELINV_OK;
     }
     h->ca_off.assign(P.ns, -1);
+    if (all_coded(h)) {
+        for (int32_t K = 0; K < P.ns; K++) h->ca_off[K] = h->sn[K].c_off;
+        h->ca_total = (int64_t)h->gcL.size();
+        h->ca_state = 1;
+        return SELINV_OK;
+    }
     int64_t used = 0;
     for (int32_t K = 0; K < P.ns; K++) {
         const int64_t cl = P.cl(K), cu = P.cu(K);
         if (cl == 0 || cu == 0) continue;
         h->ca_off[K] = used;
         used += cl * cu;
-    }
-    if (used > 0 && used == (int64_t)h->gcL.size() && all_coded(h)) {
-        // the same order and offsets: ca_off(K) = c_off(K)
-        HIPCHK(h->err, alloc_bytes(h->al, (void **)&h->d_gcA, used * sizeof(uint32_t)), "alloc gather codes");
-        HIPCHK(h->err, launch_merge_codes(h->d_sn, P.ns, h->d_gcL, h->d_gcU, h->d_gcA, nullptr), "merge gather codes");
-        HIPCHK(h->err, hipStreamSynchronize(nullptr), "merge gather codes");
-        h->ca_total = used;
-        h->ca_state = 1;
-        return SELINV_OK;
     }
     std::vector<uint32_t> codes;
     try {
@@ -1656,7 +1651,11 @@ selinv_status ensure_codes_all(selinv_handle h) {
     for (unsigned t = 1; t < nt; t++) pool.emplace_back(work);
     work();
     for (auto &t : pool) t.join();
-    HIPCHK(h->err, upload(h->al, &h->d_gcA, codes), "upload gather codes");
+    if (hipError_t e = upload(h->al, &h->d_gcA, codes); e != hipSuccess) {
+        h->al.put(h->d_gcA);  // allocated but not filled
+        h->d_gcA = nullptr;
+        return dev_fail(h->err, e, "upload gather codes");
+    }
     h->ca_total = used;
     h->ca_state = 1;
     return SELINV_OK;
@@ -3063,7 +3062,7 @@ selinv_status selinv_check_plan(selinv_handle h, int64_t *mismatches) {
                 const uint32_t want = (uint32_t)((kind == LOC_DIAG ? 1 : kind == LOC_L ? 2 : 3) << GCODE_SHIFT) |
                                       (uint32_t)off;
                 const uint32_t l = h->gcL[co + a + b * cl], u = h->gcU[co + b + a * cu];
-                bad += loc < 0 || (kind == LOC_U ? (u != want || l != 0) : (l != want || u != 0));
+                bad += loc < 0 || l != want || u != (kind == LOC_U ? want : 0u);
             }
     }
     if (bad && h->err.empty()) h->err = "push maps, levels or gather codes inconsistent with R_L / R_U";

@@ -54,3 +54,34 @@ def test_kept_policy_runs_the_policy(si, dims, cap, forks):
     assert t[6] == (0 if forks else 1)
     s.run("fp64")
     assert in_place_levels(s) == want and np.array_equal(s.get_selected(), x)
+
+
+# the levels read in place by default take their codes from the gather's own
+# array: no allocation of one code per entry of every G_K, whose failure (a
+# bounded hook) would fail a run that a stored G can do without it
+def test_in_place_levels_need_no_code_array(si):
+    import torch
+    print("[case] in-place levels under a bounded hook", flush=True)
+    refuse = []
+
+    def alloc(nbytes):
+        if any(r <= nbytes < r + 64 for r in refuse):
+            return None
+        return torch.cuda.caching_allocator_alloc(nbytes, torch.cuda.current_device())
+
+    si.set_allocator("custom", alloc=alloc, free=torch.cuda.caching_allocator_delete)
+    try:
+        w, s = grid(si, (96, 80), 64, 32)
+        s.factor(w.values)
+        st = s.structure()
+        refuse.append(4 * int((np.diff(st["rl_ptr"]) * np.diff(st["ru_ptr"])).sum()))
+        s.run("fp64")
+        assert in_place_levels(s)
+        x = s.get_selected()
+        for form in ("stored", "in_products"):
+            s.set_gather_form(form)
+            s.run("fp64")
+            assert np.array_equal(s.get_selected(), x)
+        s.close()
+    finally:
+        si.set_allocator("torch")
