@@ -240,8 +240,9 @@ selinv_status selinv_set_sweep_mode(selinv_handle h, int32_t mode);
  * the supernode's products need only those rows and columns of the blocks
  * computed before it; Theorem 1 names the blocks they lie in).
  *   0 (default): the tuning's choice per level (selinv_tune); without a
- *     tuning as 2 on the levels of thin supernodes of a plan whose every G_K
- *     has gather codes (selinv_set_gather_code_budget), a stored G elsewhere;
+ *     tuning as 2 on the levels of thin supernodes and short products of a
+ *     plan whose every G_K has gather codes
+ *     (selinv_set_gather_code_budget), a stored G elsewhere;
  *   1: a stored G: gather tiles copy G_K into a workspace that the products
  *     of steps 3 and 5 then read;
  *   2: no stored G on any level of large supernodes: the products of steps

@@ -562,26 +562,36 @@ inline bool fused_prologue(const SnRec &r) { return r.s <= 64 && r.cl <= 64 && r
 
 // Levels whose steps 3/5 read G_K from its sources without a tuning: only where
 // every G_K of the plan has gather codes (nothing is built or allocated), and
-// where a stored G gains nothing from being read again, that is where the
-// products read it once (s up to one tile).  A launch of 32-wide tiles waits
-// for its loads either way, and the gather and the push it saves count; FP64
-// levels gain up to s = 128.  A launch of 64-wide tiles gains while the products
-// are thin (s <= 32) or G_K small (tiles of the gather mostly edges).  Time of
-// the level with the step-4 launch above it, in place / stored: 2D 256^2 FP64
-// levels of 32-wide tiles 0.82-0.98 (s = 128 .. 16), mixed FP32 193x117
-// 0.84-0.99, but split-BF16 24^3 1.08-1.30 at s = 72 .. 200; complex 256^2
-// 64-wide tiles 0.79-0.88 (s = 16, 32), a batch of 12 grids 0.90-0.96 (c up to
-// 78, s = 49 .. 64) and 1.01-1.06 (c from 98, s = 64).
+// where that beats a stored G.  It saves the gather and the push, and pays one
+// more dependent load per k chunk and operands staged through registers.  Time
+// in place / stored, on bands (a chain of supernodes of s columns and c rows
+// each, m of them side by side: a level of m) and on the workloads' grids:
+// 32-wide tiles (launches that wait for their loads).
+//   FP64, s <= 128: the bands' sweep 0.79-0.99 (c = 80 .. 200, m = 1 .. 64); each
+//   level of the 2D 256^2 matrix 2-8 us of 309.  Not past c = 320 on levels of a
+//   few: c = 400 1.05 (m = 1), 1.02 (4), 0.92 (16); complex ones count c in
+//   nodes, as their products form half of the columns.
+//   Mixed, s <= 64 and c <= 160 (a stored G of half the bytes): bands of s = 16
+//   and 32 0.82-1.03 (c = 80 .. 128), 1.02-1.13 (200, m <= 16), 1.03-1.27 (400).
+//   Not where most 64x64 gather tiles take their entries from one block, which
+//   makes the gather cheap: bands of s = 64, c = 80 .. 128 1.05-1.15 (m <= 4),
+//   but 0.96 on the 2D grids 44x189 and 149x60 (s = 44 and 60).
+// 64-wide tiles.
+//   s <= 32: complex 256^2 4-9 us a level of 875; bands, mixed, 0.84-1.06.
+//   s <= 64 while G_K is small (gather tiles mostly edges): 600 bands of c = 65
+//   and 80 20 and 2-12 us a level of 469 (FP64), 15 and 0-8 of 409 (FP32), but a
+//   batch of 12 grids loses 8 (FP64) and 19 us (FP32) on its level of mean c 108.
 std::vector<char> in_place_levels(const std::vector<selinv_handle> &hs, int prec) {
     int depth = 0;
     for (auto h : hs) {
         depth = std::max(depth, h->P.nlevels);
         if (!all_coded(h)) return {};
     }
+    const bool f64 = prec == SELINV_FP64;
     std::vector<char> use(depth, 0);
     for (int d = 0; d < depth; d++) {
-        double t64 = 0, g = 0, n = 0;
-        int smax = 0;
+        double t64 = 0, g = 0, n = 0, gt = 0, gu = 0;
+        int smax = 0, cmax = 0, cnodes = 0;
         for (auto h : hs) {
             if (d >= h->P.nlevels) continue;
             for (int32_t K : h->P.levels[d]) {
@@ -592,11 +602,22 @@ std::vector<char> in_place_levels(const std::vector<selinv_handle> &hs, int prec
                 g += (double)r.cl * r.cu;
                 n += 1;
                 smax = std::max(smax, r.s);
+                cmax = std::max({cmax, r.cl, r.cu});
+                cnodes = std::max(cnodes, std::max(r.cl, r.cu) / (h->cpx_ok ? 2 : 1));
+                // gather tiles, and those of one source block (GatherTile::kind)
+                auto whole = [&](const std::vector<int32_t> &idx, int64_t at, int c) {
+                    int w = 0;
+                    for (int x = 0; x < c; x += 64)
+                        w += h->P.supof[idx[at + x]] == h->P.supof[idx[at + std::min(x + 64, c) - 1]];
+                    return w;
+                };
+                gt += std::ceil(r.cl / 64.0) * std::ceil(r.cu / 64.0);
+                gu += (double)whole(h->P.rl, h->P.rl_ptr[K], r.cl) * whole(h->P.ru, h->P.ru_ptr[K], r.cu);
             }
         }
         if (n == 0) continue;
         if (t64 < kTile32Below)
-            use[d] = smax <= (prec == SELINV_FP64 ? 128 : 64);
+            use[d] = f64 ? smax <= 128 && (cnodes <= 320 || n >= 8) : smax <= 64 && cmax <= 160 && 2 * gu <= gt;
         else
             use[d] = smax <= 32 || (smax <= 64 && g <= 6500 * n);
     }

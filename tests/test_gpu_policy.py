@@ -85,3 +85,56 @@ def test_in_place_levels_need_no_code_array(si):
         s.close()
     finally:
         si.set_allocator("torch")
+
+
+def chains(parts):
+    """Independent band matrices, `count` of n columns coupled at distances 1
+    and c: natural order gives each a chain of supernodes with about c rows."""
+    import scipy.sparse as sp
+    blocks = []
+    for count, n, c in parts:
+        r = np.random.default_rng(n + c)
+        offs = [-c, -1, 0, 1, c]
+        m = sp.diags([r.uniform(-1, 0, n - abs(k)) if k else np.full(n, 5.0) for k in offs], offs)
+        blocks += [m] * count
+    a = sp.block_diag(blocks, format="csc")
+    a.sort_indices()
+    return a.shape[0], a.indptr.astype(np.int64), a.indices.astype(np.int32), a.data
+
+
+def level_shapes(s):
+    """Per level: supernodes, widest, largest c, mean and size-weighted mean of c_L c_U."""
+    st = s.structure()
+    w, cl, cu = np.diff(st["xsup"]), np.diff(st["rl_ptr"]), np.diff(st["ru_ptr"])
+    out = []
+    for d in range(s.info["nlevels"]):
+        k = (st["level"] == d) & (cl + cu > 0)
+        g = (cl[k] * cu[k]).astype(float)
+        out.append((k.sum(), w[k].max(initial=0), max(cl[k].max(initial=0), cu[k].max(initial=0)),
+                    g.mean() if k.any() else 0.0, (g * g).sum() / g.sum() if k.any() else 0.0))
+    return out
+
+
+# long products read G_K in place only where that is faster: the mixed forms not
+# beyond c = 160, nor where the gather's tiles are whole blocks (s = 64); FP64
+# not beyond 320 on levels of a few supernodes
+@pytest.mark.parametrize("parts,cap,prec,want", [
+    ([(1, 500, 200)], 32, "mixed_fp32", False), ([(1, 500, 200)], 32, "mixed_bf16x3", False),
+    ([(1, 500, 200)], 32, "fp64", True), ([(1, 292, 100)], 32, "mixed_fp32", True),
+    ([(4, 500, 120)], 64, "mixed_fp32", False), ([(4, 500, 120)], 48, "mixed_fp32", True),
+    ([(1, 900, 400)], 64, "fp64", False), ([(8, 900, 400)], 64, "fp64", True)])
+def test_in_place_by_product_length(si, parts, cap, prec, want):
+    print("[case] in place", parts, cap, prec, flush=True)
+    n, cp, ri, v = chains(parts)
+    s = si.SelInv(n, cp, ri, None, cap, cap, 100).factor(v)
+    s.run(prec)
+    c = parts[0][2]
+    shapes = level_shapes(s)
+    full = [d for d, x in enumerate(shapes) if x[2] >= c and x[1] == cap]
+    got = in_place_levels(s)
+    assert full and all((d in got) == want for d in full), (got, shapes)
+    x = s.get_selected()
+    for form in ("stored", "in_products"):
+        s.set_gather_form(form)
+        s.run(prec)
+        assert np.array_equal(s.get_selected(), x)
