@@ -581,6 +581,9 @@ inline bool fused_prologue(const SnRec &r) { return r.s <= 64 && r.cl <= 64 && r
 //   s <= 64 while G_K is small (gather tiles mostly edges): 600 bands of c = 65
 //   and 80 20 and 2-12 us a level of 469 (FP64), 15 and 0-8 of 409 (FP32), but a
 //   batch of 12 grids loses 8 (FP64) and 19 us (FP32) on its level of mean c 108.
+//   The mixed forms weigh each G_K by its size, as a few large ones take most of
+//   a level's time: 900 bands of c = 70 with 24 of c = 250, 17 us slower in place
+//   of 750 (FP32), 13 of 725 (split-BF16), but 2 us of 849 in FP64.
 std::vector<char> in_place_levels(const std::vector<selinv_handle> &hs, int prec) {
     int depth = 0;
     for (auto h : hs) {
@@ -590,7 +593,7 @@ std::vector<char> in_place_levels(const std::vector<selinv_handle> &hs, int prec
     const bool f64 = prec == SELINV_FP64;
     std::vector<char> use(depth, 0);
     for (int d = 0; d < depth; d++) {
-        double t64 = 0, g = 0, n = 0, gt = 0, gu = 0;
+        double t64 = 0, g = 0, g2 = 0, n = 0, gt = 0, gu = 0;
         int smax = 0, cmax = 0, cnodes = 0;
         for (auto h : hs) {
             if (d >= h->P.nlevels) continue;
@@ -599,7 +602,9 @@ std::vector<char> in_place_levels(const std::vector<selinv_handle> &hs, int prec
                 if (r.cl == 0 && r.cu == 0) continue;
                 const double sc = h->cpx_ok ? r.s / 2 : r.s;  // columns formed by the products
                 t64 += std::ceil(sc / 64) * (std::ceil(r.cl / 64.0) + std::ceil(r.cu / 64.0));
-                g += (double)r.cl * r.cu;
+                const double gk = (double)r.cl * r.cu;
+                g += gk;
+                g2 += gk * gk;
                 n += 1;
                 smax = std::max(smax, r.s);
                 cmax = std::max({cmax, r.cl, r.cu});
@@ -619,7 +624,7 @@ std::vector<char> in_place_levels(const std::vector<selinv_handle> &hs, int prec
         if (t64 < kTile32Below)
             use[d] = f64 ? smax <= 128 && (cnodes <= 320 || n >= 8) : smax <= 64 && cmax <= 160 && 2 * gu <= gt;
         else
-            use[d] = smax <= 32 || (smax <= 64 && g <= 6500 * n);
+            use[d] = smax <= 32 || (smax <= 64 && (f64 ? g <= 6500 * n : g2 <= 6500 * g));
     }
     return use;
 }

@@ -138,3 +138,23 @@ def test_in_place_by_product_length(si, parts, cap, prec, want):
         s.set_gather_form(form)
         s.run(prec)
         assert np.array_equal(s.get_selected(), x)
+
+
+# a level of many thin supernodes and a few with a large G_K: the few take most
+# of the time, so the mixed forms weigh each G_K by its size
+@pytest.mark.parametrize("prec", ["mixed_fp32", "mixed_bf16x3", "fp64"])
+def test_in_place_weighs_g_by_size(si, prec):
+    import torch
+    print("[case] in place, few large G_K among many", prec, flush=True)
+    n, cp, ri, v = chains([(900, 64 * 3 + 70, 70), (24, 64 * 3 + 250, 250)])
+    s = si.SelInv(n, cp, ri, None, 64, 64, 100).factor_device(torch.from_numpy(v).cuda())
+    s.run(prec)
+    shapes = level_shapes(s)
+    d = [d for d, x in enumerate(shapes) if x[0] > 900 and x[3] < 6500 < 9000 < x[4]]
+    assert d
+    got = in_place_levels(s)
+    assert all((k in got) == (prec == "fp64") for k in d), (got, shapes)
+    x = s.get_selected()
+    s.set_gather_form("stored")
+    s.run(prec)
+    assert np.array_equal(s.get_selected(), x)
