@@ -797,13 +797,14 @@ struct DmaSmem {
 typedef __attribute__((address_space(3))) char lds_char;
 
 // One operand of such a tile: R rows (columns of op(B)) from r0 on; KC:
-// contiguous along k.
+// contiguous along k.  (The address arithmetic is also compiled for the host,
+// where a test compares it with 64-bit addresses at the largest operands.)
 template <typename T, int R, bool KC>
 struct DmaOperand {
     static constexpr int E = sizeof(T), BK = 128 / E, NI = R / 32, RB = R * E;
     // row-contiguous layout: swizzle of row k (a lane reads k = lane / 16 of 4
     // at a time, or 8 consecutive k of its quarter of 32)
-    static __device__ __forceinline__ int swz(int k) {
+    static __host__ __device__ __forceinline__ int swz(int k) {
         return ((std::is_same<T, Pk32>::value ? k >> 3 : k) & 3) * 16 * E & (RB - 1);
     }
     const char *base;   // r0, k = 0
@@ -815,7 +816,8 @@ struct DmaOperand {
     int lim;            // rows past the operand read its last one, r0 + lim
     // rows (KC) or k of one load
     static constexpr int PER = KC ? 8 : 1024 / RB;
-    __device__ __forceinline__ void init(const void *ptr, int64_t ld, int r0, int rows, int K, int lane, int wave) {
+    __host__ __device__ __forceinline__ void init(const void *ptr, int64_t ld, int r0, int rows, int K, int lane,
+                                                  int wave) {
         base = (const char *)ptr + (KC ? (int64_t)r0 * ld : (int64_t)r0) * E;
         lim = rows - 1 - r0;
         size = ((KC ? (int64_t)lim * ld + K : (int64_t)(K - 1) * ld + (lim + 1)) * E) + (16 - E);
@@ -835,12 +837,23 @@ struct DmaOperand {
             }
         }
     }
+    // Scalar offset of chunk c (narrow operands: one descriptor over [0, size)).
+    __host__ __device__ __forceinline__ int chunk_at(int c) const { return c * (int)kstep; }
+    // Descriptor of the wide form's load q = wave * NI + i of chunk c: bytes from
+    // base, and the range left there.
+    __host__ __device__ __forceinline__ int64_t load_at(int c, int q) const {
+        return c * kstep + (KC ? min(q * PER, lim) : q * PER) * rstep;
+    }
+    static __host__ __device__ __forceinline__ uint32_t range_of(int64_t left) {
+        const int32_t hi = (int32_t)(left >> 32);
+        return hi < 0 ? 0u : hi > 0 ? 0xffffffffu : (uint32_t)left;
+    }
     __device__ __forceinline__ void issue(lds_char *lds, int c, int wave) const {
         if (!wide) {
             // one descriptor, the chunk in the scalar offset
             const __amdgpu_buffer_rsrc_t rs =
                 __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, (int)size, 0x00020000);
-            const int so = c * (int)kstep;
+            const int so = chunk_at(c);
 #pragma unroll
             for (int i = 0; i < NI; i++)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
@@ -849,10 +862,8 @@ struct DmaOperand {
         }
 #pragma unroll
         for (int i = 0; i < NI; i++) {
-            const int q = wave * NI + i;
-            const int64_t off = c * kstep + (KC ? min(q * PER, lim) : q * PER) * rstep, left = size - off;
-            const int32_t hi = (int32_t)(left >> 32);
-            const uint32_t num = hi < 0 ? 0u : hi > 0 ? 0xffffffffu : (uint32_t)left;
+            const int64_t off = load_at(c, wave * NI + i);
+            const uint32_t num = range_of(size - off);
             const __amdgpu_buffer_rsrc_t rs =
                 __builtin_amdgcn_make_buffer_rsrc((void *)(base + off), 0, (int)num, 0x00020000);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
@@ -860,7 +871,7 @@ struct DmaOperand {
         }
     }
     // byte offset of element (row r, k) of a chunk
-    static __device__ __forceinline__ int at(int r, int k) {
+    static __host__ __device__ __forceinline__ int at(int r, int k) {
         if constexpr (KC)
             return r * 128 + (((k * E) / 16) ^ ((r >> 1) & 7)) * 16 + (k * E) % 16;
         else
