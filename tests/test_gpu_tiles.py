@@ -22,6 +22,9 @@ def table(levels, tile):
     return [4, levels, 1, tile, tile, tile, 0, 0] + [tile, tile, 1, 0] * levels
 
 
+# Only sum(sizes) enters the matrix below, a random pattern that fills in: its
+# supernodes are as wide as the cap, the last one the remainder.  Chosen widths
+# and sets, several in one launch, are in test_gpu_tile_shapes.py.
 def split_matrix(sizes, seed):
     """Dense diagonal blocks of the given sizes, each coupled to all later
     ones: supernode k has sizes[k] columns and c = sum(sizes[k+1:])."""
