@@ -157,14 +157,15 @@ def phase_profile(s, prec, stream, reps=5):
 
 
 KERNEL_SYMBOL = {
-    # (class, precision, tile) -> kernel symbol as rocprofv3 prints it
-    "gemm35": "selinv::gemm_v2<{mode}, {t}, {t}, {T}, {T}, 1>",
+    # (class, precision, tile) -> kernel symbol as rocprofv3 prints it; G: the
+    # type G_K and the normalised panels are stored in
+    "gemm35": "selinv::gemm_v2<{mode}, {t}, {t}, {G}, {T}, 1>",
     "gemm35g": "selinv::gemm_g35<{mode}, {t}, {t}, {T}>",
     "gemm4": "selinv::step4_gather<{mode}, {t}, {t}, {T}>",
-    "gather": "selinv::gather_kernel<{T}>",
+    "gather": "selinv::gather_kernel<{T}, {G}>",
     "small": "selinv::small_kernel<{mode}>",
     "tri": "selinv::tri_base_kernel<4> (+ doubling rounds)",
-    "norm": "selinv::gemm_v2<{pm}, *, *, double, {T}, 0>",
+    "norm": "selinv::gemm_v2<{mode}, *, *, double, {G}, 0>",
     "dt": "selinv::gemm_v2<0, *, *, double, double, 0>",
 }
 
@@ -203,9 +204,10 @@ def roofline(ph, prec):
     ovh = ph.get("event_overhead_ms", 0.0)
     mode = {"fp64": 0, "mixed_fp32": 1, "mixed_bf16x3": 2}[prec]
     T = "double" if prec == "fp64" else "float"
+    G = "selinv::Pk32" if prec == "mixed_bf16x3" else T
     r = price(g, ovh)
     r.update({"traffic": None, "class": key[0],
-              "kernel": KERNEL_SYMBOL[key[0]].format(mode=mode, t=key[1], T=T, pm=0 if prec == "fp64" else 3),
+              "kernel": KERNEL_SYMBOL[key[0]].format(mode=mode, t=key[1], T=T, G=G),
               "launches": len(g), "event_overhead_ms": ovh,
               "class_total_ms": sum(l["ms"] for l in g)})
     return r

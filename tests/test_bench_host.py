@@ -38,3 +38,27 @@ def test_roofline_takes_the_largest_class_and_names_its_kernel():
     assert r["kernel"] == "selinv::gemm_g35<2, 32, 32, float>"
     lp = bench.largest_product(ph, "mixed_bf16x3")
     assert lp["level"] in (20, 21, 5) and abs(lp["issued_frac_of_bf16_peak"] - 3 * lp["useful_tflops"] / 2500) < 1e-12
+
+
+def test_kernel_symbols_are_in_the_library():
+    """Every kernel that bench.py names is one the library launches (its host
+    stubs, which carry the kernel's name and template arguments)."""
+    import re
+    import shutil
+    import subprocess
+
+    import pytest
+
+    from paper_1708_04539_amd.selinv import LIB_PATH
+    if shutil.which("nm") is None:
+        pytest.skip("no nm")
+    out = subprocess.run(["nm", "-C", LIB_PATH], capture_output=True, text=True, check=True).stdout
+    have = set(re.findall(r"selinv::__device_stub__(\w+(?:<[^()]*>)?)", out))
+    assert have
+    for prec in ("fp64", "mixed_fp32", "mixed_bf16x3"):
+        for cls in ("tri", "norm", "dt", "small", "gather", "gemm35", "gemm35g", "gemm4"):
+            for tile in (32, 64, 128):
+                ph = {"event_overhead_ms": 0.0, "launches": [launch(cls, tile, 1, 1.0, 1e9, 1e9, 78.6)]}
+                name = bench.roofline(ph, prec)["kernel"].split(" (")[0]
+                want = re.escape(name.removeprefix("selinv::")).replace(r"\*", r"\d+")
+                assert any(re.fullmatch(want, h) for h in have), (prec, cls, tile, name)
