@@ -207,8 +207,8 @@ struct Runner {
     std::unique_ptr<Sweep> sweep[3];
     Tuning tune[3];
     int sweep_mode = 0;
-    // where G_K comes from: 0 the tuning's choice per level (stored without
-    // one), 1 always a stored G, 2 its sources inside the step-3/5 products
+    // where G_K comes from: 0 the tuning's choice per level (without one,
+    // in_place_levels), 1 always a stored G, 2 its sources inside the step-3/5 products
     // on every level that allows it
     int gather_form = 0;
     bool profiling = false;
@@ -366,19 +366,26 @@ selinv_status ensure_prec(selinv_handle h, int prec) {
 // launches with fewer 64x64 tiles than this use 32x32 tiles; with at least
 // kTile128From 128x128 tiles, 128x128 (measured on MI355X: the FP64 and FP32
 // products run faster on 64x64 tiles at every size of these workloads, the
-// split-BF16 products on 128x128 tiles once a launch has a few waves of them)
+// split-BF16 products on 128x128 tiles once a launch has a few waves of them).
+// A sweep's change in us when one launch of steps 3+5 takes the other width.
+// Below the line, 64-wide: 2D 256^2 FP64 +3 .. +14 of 313 (68 .. 492 tiles), 48^3
+// FP64 -13 .. +62 of 7930, 45x38x31 FP32 -10 .. +6 of 1555.  Above it, 32-wide:
+// 48^3 +44 .. +240 (608 .. 2550 tiles, c from 726), 45x38x31 +10 .. +72 (576 ..
+// 1400); with short products 48^3 -9 .. +24 (c below 500) and, on levels read in
+// place, a batch of 12 grids -6 .. -17 of 832, complex 256^2 -4 .. -15 of 874.
 constexpr double kTile32Below = 512;
 // levels at least this wide (in supernodes) start the part of the prologue
 // that runs beside the sweep of the levels above
 constexpr int kSplitWidth = 64;
-// The fork of that part costs 15-30 us (two queues, their joins, and the upper
+// The fork of that part costs 10-40 us (two queues, their joins, and the upper
 // levels' launches waiting for compute units) and hides its time behind the
 // levels above: without a tuning it is made only if there are at least
 // kForkLevels of them and kForkItems 64-wide inversion workgroups to hide.
-// Measured, us a run, forked against not: 2D 256^2 376 / 430 (7 levels above,
-// 1203 workgroups), 3 grids of side 77-88 195 / 218 (5, 346); 45x165 203 / 179
-// (6, none), 59x195 237 / 211 (6, 192), 12 grids of side 64-256 1129 / 1092 (3,
-// 5683), 4 grids 562 / 558 (4, 2441).
+// Measured, us a graph replay, forked / not.  The rule forks: 2D 256^2 FP64 309 /
+// 320, FP32 286 / 311; 180^2 231 / 238; complex 256^2 873 / 944; 4 grids of side
+// 90-256 506 / 515; but also 128^2 192 / 181 and 200^2 of cap 64 335 / 324.  It
+// does not: 64^2 127 / 115, 100^2 182 / 171, 150x40 136 / 121, 256^2 of cap 32
+// 588 / 570, 24^3 462 / 446, 12 grids of side 64-256 868 / 832.
 constexpr int kForkLevels = 5;
 constexpr int64_t kForkItems = 256;
 // split-K of step 4: levels whose step-4 launch has fewer 64x64 tiles than
@@ -1246,9 +1253,10 @@ selinv_status build_sweep(std::vector<selinv_handle> &hs, const DevAlloc &al, in
             S->lev_bytes_gather[d] += src;
     }
     // persistent task queue (on request only: level launches are faster at
-    // every size, 83 us against 125 us on the 2D 32^2 grid and 375 us against
-    // 930 us on 256^2, as the queue pays agent-scope release and acquire per
-    // task): level by level from the root; per level all gather tiles, then the
+    // every size, as the queue pays agent-scope release and acquire per task;
+    // eager, us: 55 against 108 on the 2D 32^2 grid, 308 against 890 on 256^2,
+    // 260 against 438 on 193x117 in FP32; 10.0 ms against 23.4 ms on a chain of
+    // 1992 levels of one supernode): level by level from the root; per level all gather tiles, then the
     // step-3 tiles, the step-5 tiles, the step-4 tiles
     S->persistent = sweep_mode == SWEEP_PERSISTENT;
     if (S->persistent) {

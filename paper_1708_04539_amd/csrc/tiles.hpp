@@ -757,8 +757,8 @@ __device__ __forceinline__ void gemm_tile_g35(const GemmProb &p, const int m0, c
 // ---------------------------------------------------------------------------
 // Product tiles whose operands go from memory straight into LDS
 // ---------------------------------------------------------------------------
-// The FP64 and FP32 products of 64-wide tiles (and the FP32 ones of 128-wide
-// tiles), for operands stored in the arithmetic's own type.  What bound the
+// The products of 64-wide tiles (and the FP32 and split-BF16 ones of 128-wide
+// tiles) whose operands are stored as Mode::G.  What bound the FP64 and FP32
 // register-staged tile there was not the matrix pipe but the vector
 // instructions beside it: v_mfma_f64 does not run beside other VALU work of
 // its SIMD (SQ_VALU_MFMA_COEXEC_CYCLES 0), and every staged element cost three
@@ -767,26 +767,31 @@ __device__ __forceinline__ void gemm_tile_g35(const GemmProb &p, const int m0, c
 // scalar offset, the lane's offset a constant register, and the k loop holds
 // MFMAs and LDS reads only.  Measured on the steps-3/5 launches of the 3D 64^3
 // 27-point matrix (1.64 TFLOP): FP64 29.9 -> 25.3 ms (65 TFLOP/s, MFMA busy
-// 78 -> 92 % of the SIMD cycles), FP32 17.3 -> 12.9 ms (127 TFLOP/s).  A third
+// 78 -> 92 % of the SIMD cycles), FP32 17.3 -> 12.9 ms (127 TFLOP/s), split-BF16
+// 8.7 -> 6.4 ms with its operands split where they are written.  A third
 // stage (three workgroups per compute unit instead of five) 28.6 ms where two
 // took 27.8 ms; 128-wide FP64 tiles (two workgroups per compute unit, a
 // quarter of the tiles to balance) 33.5 ms.
 //
-// A chunk is 128 bytes of k (16 FP64, 32 FP32) of every row of op(A) and
-// column of op(B); one wavefront-wide load moves 1 KB.  The load writes lane
-// l's 16 bytes at l * 16, so the layout is swizzled on the source side, in
-// units of 16 bytes, to spread the MFMA operand reads over the banks:
+// A chunk is 128 bytes of k (16 FP64, 32 FP32 or split-BF16 words) of every row
+// of op(A) and column of op(B); one wavefront-wide load moves 1 KB.  The load
+// writes lane l's 16 bytes at l * 16, so the layout is swizzled on the source
+// side, in units of 16 bytes:
 //   contiguous along k (A with op = T, B with op = N): row r holds its 128
 //     bytes at r * 128, unit u at place u ^ ((r >> 1) & 7);
 //   contiguous along the rows: row k of the chunk holds its R elements at
-//     k * R * E, byte m * E at (m * E) ^ ((k & 3) * 16 E): the four k of an
-//     operand read fall on different bank groups.
+//     k * R * E, byte m * E at (m * E) ^ ((k & 3) * 16 E) (split-BF16: k / 8 for
+//     k), so that the k of an operand read differ in place.
+// That spreads the MFMA operand reads over more banks, not over all: the
+// counters show 5.9 conflict cycles per LDS instruction on the 64-wide FP64
+// steps-3/5 kernel (0 with the padded rows of the register-staged layout), which
+// its matrix pipe hides, and 2.4 on the 128-wide split-BF16 one.
 // Two LDS stages: chunk c + 1 is issued after the barrier that ends chunk
 // c - 1, one barrier per chunk.  Rows past the operand are read as its last
 // row (k-contiguous) or as whatever follows them, zeros past the operand's end
 // (the buffer's range); they only reach results that are not stored.  The k
 // past the operand in the last chunk are cleared in LDS before they are used,
-// up to the next multiple of 4; the MFMAs beyond are left out.  The products
+// up to the next whole MFMA (4; split-BF16 32); the MFMAs beyond are left out.  The products
 // are those of the register-staged tile in the same order, so the results are
 // equal bit for bit.
 template <int BM, int BN>
