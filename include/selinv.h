@@ -203,7 +203,8 @@ selinv_status selinv_factor(selinv_handle h, const double *values);
  * factors in one workgroup, the solves of the block and panel rows as
  * products with them, trailing GEMM updates), then W_K = -L(R_L,K) U(K,R_U)
  * for every supernode of the level, added atomically to the blocks of the
- * ancestors by the launch that forms it (right-looking supernodal LU; supernodes of one level are
+ * ancestors by the launch that forms it (right-looking supernodal LU;
+ * supernodes of one level are
  * independent).  FP64 throughout; rounding differs from selinv_factor (the
  * solves multiply by tile inverses, sums run in another order).  The first
  * call builds and uploads its work lists (host range checks included).  A
@@ -251,7 +252,8 @@ selinv_status selinv_set_sweep_mode(selinv_handle h, int32_t mode);
  *     gather codes of a plan whose every G_K has them
  *     (selinv_set_gather_code_budget), else codes built on the first such
  *     run, c_L c_U per supernode, 4 bytes each, in device memory from the
- *     handle's allocator (SELINV_E_NOMEM when that fails).  Levels run by the fused small-supernode launch keep G_K in
+ *     handle's allocator (SELINV_E_NOMEM when that fails).  Levels run by
+ *     the fused small-supernode launch keep G_K in
  *     LDS, and the persistent sweep always gathers into G.
  * The results of forms 1 and 2 are equal bit for bit (the same values in the
  * same order).  form outside 0..2: SELINV_E_INVALID_ARG.  Changing the form
@@ -283,13 +285,13 @@ selinv_status selinv_set_gather_form(selinv_handle h, int32_t form);
  *     drains).
  * Each configuration runs reps + 1 times (the first untimed; 1 <= reps <=
  * 100) and counts its fastest run: per-launch times from eager runs with
- * events, whole-sweep comparisons from replays of the sweep's HIP graph.  When the measured choices are not faster
- * than the built-in size policy, the policy is kept: the table then has tile
- * edges 0 and the prologue placement and in-place levels that the policy
- * takes without a table.  ms_policy and ms_tuned
- * (nullable) receive the two sweep times.  Needs a factored handle; the runs
- * leave the results of an ordinary run behind.  Batches have their own
- * tables (selinv_batch_tune). */
+ * events, whole-sweep comparisons from replays of the sweep's HIP graph.
+ * When the measured choices are not faster than the built-in size policy,
+ * the policy is kept: the table then has tile edges 0 and the prologue
+ * placement and in-place levels that the policy takes without a table.
+ * ms_policy and ms_tuned (nullable) receive the two sweep times.  Needs a
+ * factored handle; the runs leave the results of an ordinary run behind.
+ * Batches have their own tables (selinv_batch_tune). */
 selinv_status selinv_tune(selinv_handle h, selinv_precision prec, int32_t reps, void *stream,
                           double *ms_policy, double *ms_tuned);
 

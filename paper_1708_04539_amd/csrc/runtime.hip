@@ -208,7 +208,8 @@ struct Runner {
     Tuning tune[3];
     int sweep_mode = 0;
     // where G_K comes from: 0 the tuning's choice per level (without one,
-    // in_place_levels), 1 always a stored G, 2 its sources inside the step-3/5 products
+    // in_place_levels), 1 always a stored G, 2 its sources inside the step-3/5
+    // products
     // on every level that allows it
     int gather_form = 0;
     bool profiling = false;
@@ -1256,7 +1257,8 @@ selinv_status build_sweep(std::vector<selinv_handle> &hs, const DevAlloc &al, in
     // every size, as the queue pays agent-scope release and acquire per task;
     // eager, us: 55 against 108 on the 2D 32^2 grid, 308 against 890 on 256^2,
     // 260 against 438 on 193x117 in FP32; 10.0 ms against 23.4 ms on a chain of
-    // 1992 levels of one supernode): level by level from the root; per level all gather tiles, then the
+    // 1992 levels of one supernode): level by level from the root; per level
+    // all gather tiles, then the
     // step-3 tiles, the step-5 tiles, the step-4 tiles
     S->persistent = sweep_mode == SWEEP_PERSISTENT;
     if (S->persistent) {
